@@ -191,13 +191,14 @@ size_t sr_tree_verify_attn_workspace(const sr_attn_desc* desc);
  * block_table entries past its last page. Invalid trajectory (ctx_len out of
  * range, a page id outside [0,num_blocks), bad topology): out and lse are NaN.
  * Workspace: the partial results of prefixes that are cut over several blocks
- * (two per block) and where each trajectory lies in the cut, written by the call
- * itself (no initialisation by the caller, no memset). A smaller workspace is
- * taken down to one partial result per prefix chunk of 32, 128 or 256 pages (by
- * the number of (trajectory, KV head, row group) triples: below 64, below 512,
- * more; none for prefixes of one chunk), with less even work over the blocks. Two
- * calls that share a workspace must not run concurrently (on one stream they
- * don't).
+ * (at most two per block, each of the query rows that a KV head has) and where
+ * each trajectory lies in the cut, written by the call itself (no initialisation
+ * by the caller, no memset). A smaller workspace is taken down to one partial
+ * result per prefix chunk of 32, 128 or 256 pages (by the number of (trajectory,
+ * KV head, row group) triples: below 64, below 512, more; none for prefixes of
+ * one chunk) and, for bf16, 8 bytes per chunk and 12 more, with less even work
+ * over the blocks. Two calls that share a workspace must not run concurrently (on
+ * one stream they don't).
  */
 sr_status sr_tree_verify_attn(const sr_attn_desc* desc,
                               const void* q, const void* k_cache, const void* v_cache,

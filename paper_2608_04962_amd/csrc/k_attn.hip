@@ -116,7 +116,7 @@ struct AttnArgs {
   long long* work;                     // [0] tiles per range, [1 + b] position of trajectory b's first tile
   int B, T_, Hq, Hkv, max_blocks, num_blocks;
   float scale_log2;
-  int R, row_groups, group_rows, n_ranges, min_tiles, unit_cost, whole;
+  int R, row_groups, group_rows, n_ranges, min_tiles, unit_cost, whole, by_unit;
 };
 
 // 64-key tiles of each unit of a trajectory (one for an invalid ctx_len: its unit then writes NaN rows)
@@ -212,9 +212,15 @@ __device__ __forceinline__ AttnStart attn_start(AttnPlanLds& p, const AttnArgs<T
   return s;
 }
 
+// Partial result of the piece that range r has of unit j of trajectory b: 2 r for a piece at the range's start, 2 r + 1
+// for one that the range's end cuts off; or, with fewer units than ranges (by_unit), r + the unit's number, which
+// grows from piece to piece along the line, so every piece has its own.
+__device__ __forceinline__ int attn_slot(int by_unit, int units, int r, int b, int j, bool first) {
+  return by_unit ? r + b * units + j : 2 * r + (first ? 0 : 1);
+}
+
 // Segments of range r, in order: f(b, j, ta, n, slot, k) for tiles [ta, ta + n) of unit j of trajectory b, the k-th of
-// the range; slot = -1 for a whole unit, else the index of its partial result: 2 r for the segment at the
-// range's start, 2 r + 1 for one that the range's end cuts off. Whole block, uniform.
+// the range; slot = -1 for a whole unit, else the index of its partial result (attn_slot). Whole block, uniform.
 template <typename T, class F>
 __device__ __forceinline__ void attn_walk(AttnPlanLds& p, const AttnArgs<T>& a, long long total, long long len, int r,
                                           bool store, F f) {
@@ -232,7 +238,7 @@ __device__ __forceinline__ void attn_walk(AttnPlanLds& p, const AttnArgs<T>& a, 
       if (s.left <= 0 && !a.whole) break;
     }
     const int n = a.whole ? s.t : min(s.t - s.ta, s.left);
-    f(s.b, s.j, s.ta, n, n == s.t ? -1 : 2 * r + (k > 0 ? 1 : 0), k);
+    f(s.b, s.j, s.ta, n, n == s.t ? -1 : attn_slot(a.by_unit, units, r, s.b, s.j, k == 0), k);
     ++k;
     s.left -= n;
     s.ta = 0;                                   // a cut unit's rest belongs to the next range
@@ -1001,7 +1007,7 @@ __device__ __forceinline__ int attn_range_dma(unsigned char (&ring)[4][2 * DmaGe
       if (i.left <= 0 && !a->whole) return false;
     }
     i.n = a->whole ? i.t : min(i.t - i.ta, i.left);
-    i.slot = i.n == i.t ? -1 : 2 * r + (i.head ? 0 : 1);
+    i.slot = i.n == i.t ? -1 : attn_slot(a->by_unit, a->Hkv * a->row_groups, r, i.b, i.j, i.head);
     const AttnSeg sg = attn_seg(uload(a->ctx_len, i.b), a->max_blocks, i.ta, i.n);
     i.ctx_ok = sg.ctx_ok;
     i.tree0 = sg.tree0;
@@ -1589,7 +1595,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(const int32_t* __restrict_
                                                       const float* __restrict__ part_o,
                                                       const float* __restrict__ part_ml, float* __restrict__ out,
                                                       float* __restrict__ lse, int T_, int Hq, int Hkv,
-                                                      int max_blocks, int R, int row_groups, int group_rows, int unit_cost) {
+                                                      int max_blocks, int R, int row_groups, int group_rows, int unit_cost, int by_unit) {
   constexpr int TPR = D / 4;                 // threads per row (4 floats each)
   constexpr int RPB = 256 / TPR;             // rows per block (all of one row group: groups are whole 32s)
   const int g = blockIdx.y, b = blockIdx.z;
@@ -1618,8 +1624,9 @@ __global__ __launch_bounds__(256) void k_attn_combine(const int32_t* __restrict_
     f32x4 po[CGRP];
 #pragma unroll
     for (int k = 0; k < CGRP; ++k) {
-      // a piece at its range's start is partial 2 i of range i, one that the range's end cuts off 2 i + 1
-      const size_t pr = (size_t)(2 * (i0 + c0 + k) + (c0 + k == 0 && i0 * len < uv ? 1 : 0)) * group_rows + rr;
+      const int slot = attn_slot(by_unit, Hkv * row_groups, (int)i0 + c0 + k, b, g * row_groups + rg,
+                                 c0 + k > 0 || i0 * len >= uv);
+      const size_t pr = (size_t)slot * group_rows + rr;
       if (c0 + k < n_chunks) {
         ml[k] = *(const float2*)(part_ml + pr * 2);
         po[k] = *(const f32x4*)(part_o + pr * D + d4);
@@ -1661,8 +1668,9 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   p.R = d.T * (d.Hq / d.Hkv);
   p.Rpad = (p.R + 31) / 32 * 32;
   // bf16: more than 224 rows split evenly into groups of at most 224, so every work item keeps a wave
-  // free of query rows to issue its DMA (fp32: groups of 256)
-  p.group_rows = ATT_ROWS;
+  // free of query rows to issue its DMA (fp32: groups of 256). Fewer rows are one group of whole 32s: group_rows is
+  // also the stride of the partial results, so their scratch follows the rows there are.
+  p.group_rows = std::min(p.Rpad, ATT_ROWS);
   if (d.dtype == SR_BF16 && p.R > ATT_ROWS - 32) {
     const int ng = (p.R + (ATT_ROWS - 32) - 1) / (ATT_ROWS - 32);
     p.group_rows = ((p.R + ng - 1) / ng + 31) / 32 * 32;
@@ -1677,17 +1685,23 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   const long long tiles = units * (most + ATT_UNIT_COST);
   p.min_tiles = d.dtype == SR_BF16 ? ATT_MIN_TILES : 1;
   p.unit_cost = d.dtype == SR_BF16 ? ATT_UNIT_COST : 1;
-  p.n_ranges = std::min(tiles, std::max<long long>(ATT_BLOCKS, (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES));
+  const long long table = (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES;   // least ranges whose page ids fit the table
+  const long long ranges = std::min(tiles, std::max<long long>(ATT_BLOCKS, table));
+  p.n_ranges = ranges;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t row_bytes = (size_t)p.group_rows * (d.D + 2) * sizeof(float);   // one partial result
+  const size_t work_bytes = up((size_t)(1 + d.B) * sizeof(long long));
+  // Two partial results per range, or, with fewer units than ranges, one per range and one per unit.
   auto sizes = [&]() {
-    const size_t rows = (size_t)2 * (size_t)p.n_ranges * p.group_rows;
-    p.part_o_bytes = p.whole ? 0 : up(rows * d.D * sizeof(float));
-    p.part_ml_bytes = p.whole ? 0 : up(rows * 2 * sizeof(float));
-    p.work_bytes = p.whole ? 0 : up((size_t)(1 + d.B) * sizeof(long long));
+    p.by_unit = units < p.n_ranges;
+    const size_t rows = p.whole ? 0 : (size_t)(p.n_ranges + std::min(units, p.n_ranges)) * p.group_rows;
+    p.part_o_bytes = rows * d.D * sizeof(float);       // whole 256-byte lines: group_rows is a multiple of 32
+    p.part_ml_bytes = rows * 2 * sizeof(float);
+    p.work_bytes = p.whole ? 0 : work_bytes;
   };
   sizes();
   // The least workspace a call takes: the size of one partial result per prefix chunk of 32, 128 or 256 pages and,
-  // for bf16, two lists of the chunks. A workspace between that and the sizes above gets fewer ranges.
+  // for bf16, of two lists of the chunks. A workspace between that and the sizes above gets fewer ranges.
   const int cp = units < 64 ? 32 : units < 512 ? 128 : 256;
   const size_t nch = std::max(1, (d.max_blocks + cp - 1) / cp);
   const size_t crows = (size_t)d.B * d.Hkv * nch * p.Rpad;
@@ -1695,13 +1709,19 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
                 (d.dtype == SR_BF16 ? up((size_t)(3 + 2 * units * (long long)nch) * sizeof(unsigned)) : 0);
   p.full_bytes = std::max(p.part_o_bytes + p.part_ml_bytes + p.work_bytes, p.min_bytes);
   if (avail < p.full_bytes && !p.whole) {
-    const size_t row2 = (size_t)2 * p.group_rows * (d.D + 2) * sizeof(float), fixed = p.work_bytes + 512;
-    const long long fit = avail > fixed ? (long long)((avail - fixed) / row2) : 0;
-    p.n_ranges = std::min(p.n_ranges, fit);
-    // too little for ranges whose page ids fit the LDS table: no partial results at all (prefixes of one chunk)
-    if (p.n_ranges < 1 || (tiles + p.n_ranges - 1) / p.n_ranges > ATT_SEG_TILES) {
-      p.whole = true;
-      p.n_ranges = std::min(tiles, std::max<long long>(ATT_BLOCKS, (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES));
+    const long long parts = avail > work_bytes ? (long long)std::min<size_t>((avail - work_bytes) / row_bytes, INT32_MAX) : 0;
+    p.n_ranges = std::min(ranges, std::max(parts - units, parts / 2));
+    // Units are left whole when that keeps more blocks busy than the ranges that fit, but never a unit whose page ids
+    // would not fit the table. The least workspace always holds ranges that do (2 chunks of at most 64 tiles, and
+    // what a unit has beside them, per range); should one not, the call is refused.
+    if (p.n_ranges < table || p.n_ranges < std::min<long long>(units, ATT_BLOCKS)) {
+      if (most <= ATT_SEG_TILES) {
+        p.whole = true;
+        p.n_ranges = ranges;
+      } else if (p.n_ranges < table) {
+        p.n_ranges = table;
+        p.min_bytes = p.full_bytes;
+      }
     }
     sizes();
   }
@@ -1716,7 +1736,7 @@ static sr_status launch_attn_t(const sr_attn_desc& d, const AttnPlan& p, const v
   if (p.n_ranges > INT32_MAX / 4) return SR_ERR_INVALID;
   const AttnArgs<T> a = {(const T*)q, (const T*)kc, (const T*)vc, bt, cl, (const T*)kt, (const T*)vt, par, out, lse, po, pml,
                          work, d.B, d.T, d.Hq, d.Hkv, d.max_blocks, d.num_blocks, d.scale * kLog2e, p.R, p.row_groups,
-                         p.group_rows, (int)p.n_ranges, p.min_tiles, p.unit_cost, p.whole ? 1 : 0};
+                         p.group_rows, (int)p.n_ranges, p.min_tiles, p.unit_cost, p.whole ? 1 : 0, p.by_unit ? 1 : 0};
   const dim3 grid((unsigned)std::min<long long>(p.n_ranges, ATT_BLOCKS));
   if constexpr (sizeof(T) == 2) {
     SR_LAUNCH("sr_tree_attn", (k_tree_attn_dma<D>), grid, dim3(ATT_NW * 64), 0, s, a);
@@ -1729,7 +1749,7 @@ static sr_status launch_attn_t(const sr_attn_desc& d, const AttnPlan& p, const v
     constexpr int RPB = 256 / (D / 4);
     dim3 cgrid((p.R + RPB - 1) / RPB, d.Hkv, d.B);
     SR_LAUNCH("sr_attn_combine", (k_attn_combine<D>), cgrid, dim3(256), 0, s, cl, (const long long*)work, po, pml, out, lse,
-              d.T, d.Hq, d.Hkv, d.max_blocks, p.R, p.row_groups, p.group_rows, a.unit_cost);
+              d.T, d.Hq, d.Hkv, d.max_blocks, p.R, p.row_groups, p.group_rows, a.unit_cost, a.by_unit);
   }
   return SR_OK;
 }

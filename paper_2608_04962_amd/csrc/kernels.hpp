@@ -27,13 +27,14 @@ struct AttnPlan {
   int R;            // query rows per (trajectory, KV head) = T * Hq / Hkv
   int Rpad;         // R rounded up to 32
   int row_groups;   // blocks along the rows
-  int group_rows;   // query rows per row group (a multiple of 32, at most 256)
+  int group_rows;   // query rows per row group and per partial result (a multiple of 32, at most 256)
   bool whole;       // units are not cut: no partial results and no merge
   int min_tiles;    // least 64-key tiles of a range
   int unit_cost;    // what a unit counts for beside its tiles when ranges are cut
   long long n_ranges;   // ranges the call's tiles are cut into (at most)
-  size_t part_o_bytes, part_ml_bytes, work_bytes;   // the scratch in use: two partial results per range, the cut
+  size_t part_o_bytes, part_ml_bytes, work_bytes;   // the scratch in use: partial results, the cut
   size_t min_bytes, full_bytes;   // least workspace a call takes; what the workspace query answers
+  bool by_unit;     // partial results are numbered by range and unit (attn_slot), not two to a range
 };
 AttnPlan attn_plan(const sr_attn_desc& d, size_t avail);   // avail: bytes of workspace the call has
 sr_status launch_tree_attn(const sr_attn_desc& d, const AttnPlan& p, const void* q, const void* k_cache,

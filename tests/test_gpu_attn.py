@@ -284,3 +284,82 @@ def test_least_workspace(dt):
         ro, rl = _oracle(inp)
         assert row_rel_err(out.cpu().numpy(), ro).max() <= tol_for(dt)
         assert np.abs(lse.cpu().numpy() - rl).max() <= tol_for(dt)
+
+
+def _pooled_inputs(dt, B, T, Hq, Hkv, D, lens, max_blocks, pool, seed):
+    """Inputs whose block tables draw their pages from a small pool, so that contexts may be as long as a table
+    holds; past a trajectory's last page the table holds ids out of range."""
+    rng = np.random.default_rng(seed)
+    mk = lambda *s: synth.as_dtype(rng.standard_normal(s).astype(np.float32), dt)
+    bt = np.full((B, max_blocks), -7, np.int32)
+    for b, n in enumerate(lens):
+        bt[b, :-(-n // 16)] = rng.integers(0, pool, size=-(-n // 16))
+    par = np.array([-1] + [(i - 1) // 2 for i in range(1, T)], np.int32)
+    return dict(dtype=dt, q=mk(B, T, Hq, D), k_cache=mk(pool, Hkv, 16, D), v_cache=mk(pool, Hkv, 16, D), block_table=bt,
+                ctx_len=np.array(lens, np.int32), k_tree=mk(B, T, Hkv, D), v_tree=mk(B, T, Hkv, D),
+                parents=np.tile(par, (B, 1)), scale=D ** -0.5)
+
+
+def _call_ws(inp, size, fill=0xAB):
+    """The C call with a workspace of size bytes (None: sr_tree_verify_attn_noalloc): status, out, lse."""
+    import ctypes as C
+    from paper_2608_04962_amd import _lib
+    keys = ("q", "k_cache", "v_cache", "block_table", "ctx_len", "k_tree", "v_tree", "parents")
+    t = {k: dev_tensor(inp[k]) for k in keys}
+    desc = sr.attn_desc(t["q"], t["k_cache"], t["block_table"], inp["scale"])
+    out = torch.full(tuple(t["q"].shape), 7.0, device="cuda")
+    lse = torch.full(tuple(t["q"].shape[:3]), 7.0, device="cuda")
+    args = [C.byref(desc)] + [t[k].data_ptr() for k in keys] + [out.data_ptr(), lse.data_ptr()]
+    if size is None:
+        st = _lib.lib().sr_tree_verify_attn_noalloc(*args, None)
+    else:
+        ws = torch.full((max(size, 1),), fill, dtype=torch.uint8, device="cuda")
+        st = _lib.lib().sr_tree_verify_attn(*args, ws.data_ptr() if size else None, size, None)
+    torch.cuda.synchronize()
+    return st, out.cpu().numpy(), lse.cpu().numpy()
+
+
+def _check_nodes(inp, out, lse, nodes):
+    ro, rl = _oracle(inp, nodes)
+    sel = ~np.isnan(ro[..., 0])
+    assert np.isfinite(out).all()
+    assert row_rel_err(out[sel], ro[sel]).max() <= tol_for(inp["dtype"])
+    assert np.abs(lse[sel] - rl[sel]).max() <= tol_for(inp["dtype"])
+
+
+@pytest.mark.parametrize("dt,B,T,G,D,max_blocks,wide", [
+    ("f32", 64, 8, 4, 64, 8192, False),        # 512 units: the least workspace of tables wider than the page-id table
+    ("bf16", 64, 8, 4, 64, 8192, True),        # the same, with V that is recomputed in fp32
+    ("f32", 1, 8, 4, 128, 512, False),         # one unit of 16 chunks
+    ("bf16", 3, 8, 2, 128, 700, True),
+])
+def test_least_workspace_of_long_tables(dt, B, T, G, D, max_blocks, wide):
+    """The least workspace with few query rows and many chunks: a segment longer than the page-id table is never made,
+    also for contexts past 65536 keys, and no scratch is used past the workspace's end."""
+    Hkv = 8 if B == 64 else 1
+    top = max_blocks * 16
+    lens = [top, top - 15, top * 5 // 8 + 3] + [(37 * b) % 500 for b in range(B)]
+    inp = _pooled_inputs(dt, B, T, Hkv * G, Hkv, D, lens[:B], max_blocks, 40, seed=41)
+    if wide:
+        inp["v_cache"] = synth.as_dtype((synth.to_f64(inp["v_cache"], dt) * 1e5).astype(np.float32), dt)
+        inp["v_tree"] = synth.as_dtype((synth.to_f64(inp["v_tree"], dt) * 1e5).astype(np.float32), dt)
+    units = B * Hkv
+    nch = -(-max_blocks // (32 if units < 64 else 256))
+    rows = units * nch * (-(-T * G // 32) * 32)
+    up = lambda x: -(-x // 256) * 256
+    size = up(rows * D * 4) + up(rows * 8) + (up((3 + 2 * units * nch) * 4) if dt == "bf16" else 0)
+    st, out, lse = _call_ws(inp, size)
+    assert st == 0
+    _check_nodes(inp, out, lse, [(b, u) for b in sorted({0, B // 2, B - 1, min(1, B - 1)}) for u in (0, T - 1)])
+    st, _, _ = _call_ws(inp, size - 256)
+    assert st == 3                              # SR_ERR_WORKSPACE
+
+
+def test_noalloc_least_scratch_of_long_tables():
+    """sr_tree_verify_attn_noalloc where only the least scratch fits its array, with a context past 65536 keys."""
+    B, T, Hkv, G, D, mb = 64, 8, 8, 4, 64, 15872
+    lens = [mb * 16, 70001, 65537] + [(53 * b) % 700 for b in range(B)]
+    inp = _pooled_inputs("f32", B, T, Hkv * G, Hkv, D, lens[:B], mb, 24, seed=42)
+    st, out, lse = _call_ws(inp, None)
+    assert st == 0
+    _check_nodes(inp, out, lse, [(b, u) for b in (0, 1, 2, 3, 63) for u in (0, T - 1)])
