@@ -346,7 +346,9 @@ sr_status sr_tree_verify_attn(const sr_attn_desc* d, const void* q, const void* 
                               size_t workspace_bytes, void* stream) {
   sr_status st = check_attn_args(d, q, k_cache, v_cache, block_table, ctx_len, k_tree, v_tree, parents, out);
   if (st != SR_OK) return st;
-  const AttnPlan p = attn_plan(*d, workspace ? workspace_bytes : 0);
+  // a call that needs no workspace takes any pointer; one that is not aligned is not used
+  const bool usable = workspace != nullptr && ((uintptr_t)workspace & 255u) == 0;
+  const AttnPlan p = attn_plan(*d, usable ? workspace_bytes : 0);
   st = check_ws(workspace, workspace_bytes, p.min_bytes);
   if (st != SR_OK) return st;
   return run_attn(d, p, q, k_cache, v_cache, block_table, ctx_len, k_tree, v_tree, parents, out, lse,

@@ -300,8 +300,10 @@ def _pooled_inputs(dt, B, T, Hq, Hkv, D, lens, max_blocks, pool, seed):
                 parents=np.tile(par, (B, 1)), scale=D ** -0.5)
 
 
-def _call_ws(inp, size, fill=0xAB):
-    """The C call with a workspace of size bytes (None: sr_tree_verify_attn_noalloc): status, out, lse."""
+def _call_ws(inp, size, shift=0):
+    """The C call with a workspace of size bytes, shift bytes past an aligned address (None:
+    sr_tree_verify_attn_noalloc): status, out, lse. Asserts that nothing around the workspace is written, nor the
+    workspace itself when it is not aligned."""
     import ctypes as C
     from paper_2608_04962_amd import _lib
     keys = ("q", "k_cache", "v_cache", "block_table", "ctx_len", "k_tree", "v_tree", "parents")
@@ -313,8 +315,10 @@ def _call_ws(inp, size, fill=0xAB):
     if size is None:
         st = _lib.lib().sr_tree_verify_attn_noalloc(*args, None)
     else:
-        ws = torch.full((max(size, 1),), fill, dtype=torch.uint8, device="cuda")
-        st = _lib.lib().sr_tree_verify_attn(*args, ws.data_ptr() if size else None, size, None)
+        ws = torch.full((256 + shift + size + 4096,), 0xAB, dtype=torch.uint8, device="cuda")
+        st = _lib.lib().sr_tree_verify_attn(*args, ws.data_ptr() + 256 + shift if size else None, size, None)
+        free = ws[256 + size:] if shift == 0 else ws
+        assert bool((free == 0xAB).all()) and bool((ws[:256] == 0xAB).all())
     torch.cuda.synchronize()
     return st, out.cpu().numpy(), lse.cpu().numpy()
 
@@ -363,3 +367,18 @@ def test_noalloc_least_scratch_of_long_tables():
     st, out, lse = _call_ws(inp, None)
     assert st == 0
     _check_nodes(inp, out, lse, [(b, u) for b in (0, 1, 2, 3, 63) for u in (0, T - 1)])
+
+
+def test_workspace_that_is_not_aligned():
+    """fp32 prefixes of one chunk need no workspace and take any: one that is not aligned is left alone. Calls that
+    need one refuse it."""
+    inp = _pooled_inputs("f32", 3, 8, 8, 4, 64, [500, 0, 317], 32, 40, seed=43)
+    st, want, wl = _call_ws(inp, 0)
+    assert st == 0
+    for shift in (4, 16, 128):
+        st, out, lse = _call_ws(inp, 4 << 20, shift)
+        assert st == 0
+        assert np.array_equal(out, want) and np.array_equal(lse, wl)
+    _check_nodes(inp, want, wl, [(b, u) for b in range(3) for u in range(8)])
+    inp = _pooled_inputs("f32", 3, 8, 8, 4, 64, [500, 0, 317], 80, 40, seed=43)
+    assert _call_ws(inp, 4 << 20, 64)[0] == 1   # SR_ERR_INVALID
