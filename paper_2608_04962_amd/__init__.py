@@ -194,10 +194,15 @@ def tree_verify_attn(q, k_cache, v_cache, block_table, ctx_len, k_tree, v_tree, 
     if want_lse and lse is None:
         lse = torch.empty((B, T, Hq), dtype=torch.float32, device=dev)
     desc = attn_desc(q, k_cache, block_table, scale)
-    ws, wsb = _workspace(attn_workspace_bytes(desc), dev, workspace)
+    if workspace is None:
+        ws, wsb = _workspace(attn_workspace_bytes(desc), dev, None)
+    else:                                   # the call itself says what it takes, down to less than the query's answer
+        ws, wsb = workspace, workspace.numel() * workspace.element_size()
     st = lib().sr_tree_verify_attn(C.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
                                    _ptr(ctx_len), _ptr(k_tree), _ptr(v_tree), _ptr(parents), _ptr(out),
                                    _ptr(lse), _ptr(ws), wsb, _stream(dev))
+    if st == _lib.SR_ERR_WORKSPACE and workspace is not None:
+        raise ValueError(_lib.last_error())
     check(st, "sr_tree_verify_attn")
     return out, lse
 

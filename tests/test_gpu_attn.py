@@ -382,3 +382,22 @@ def test_workspace_that_is_not_aligned():
     _check_nodes(inp, want, wl, [(b, u) for b in range(3) for u in range(8)])
     inp = _pooled_inputs("f32", 3, 8, 8, 4, 64, [500, 0, 317], 80, 40, seed=43)
     assert _call_ws(inp, 4 << 20, 64)[0] == 1   # SR_ERR_INVALID
+
+
+def test_python_takes_the_least_workspace():
+    """tree_verify_attn takes a workspace that the call takes, smaller than the query's answer; a smaller one still is
+    a ValueError. A prefix of one chunk takes any."""
+    for lens, mb, rows in (([3000, 17, 900, 4096], 256, 16 * 8 * 32), ([500, 0, 317, 31], 32, 0)):
+        inp = _pooled_inputs("f32", 4, 8, 16, 4, 128, lens, mb, 40, seed=44)
+        t = {k: dev_tensor(v) for k, v in inp.items() if isinstance(v, np.ndarray)}
+        size = rows * (128 + 2) * 4             # 16 units, 32 rows each, a chunk per 32 pages
+        assert size < sr.attn_workspace_bytes(sr.attn_desc(t["q"], t["k_cache"], t["block_table"]))
+
+        def call(n):
+            return sr.tree_verify_attn(t["q"], t["k_cache"], t["v_cache"], t["block_table"], t["ctx_len"], t["k_tree"],
+                                       t["v_tree"], t["parents"], workspace=torch.empty(n, dtype=torch.uint8, device="cuda"))
+        out, lse = call(size)
+        _check_nodes(inp, out.cpu().numpy(), lse.cpu().numpy(), [(b, u) for b in range(4) for u in (0, 7)])
+        if size:
+            with pytest.raises(ValueError, match="workspace"):
+                call(size - 256)
