@@ -1463,8 +1463,9 @@ __global__ __launch_bounds__(ACC_NT) void k_tree_accept(const T* __restrict__ lo
       // 60.4 -> 55.4 us plain; a slot test had cost a float64 exponential, two wave sums and four divisions.)
       // The residual is kept unnormalised, with its normaliser Zc: r = R / Zc, rest / Zc outside the children.
       // q_{u,j} is the softmax of the draft logits over children j..m-1: weights relative to the largest of
-      // all children and their suffix sums, formed once. (A suffix that would underflow -- logits more than
-      // 600 apart -- takes its own maximum at every slot.)
+      // all children and their suffix sums, formed once. (With a weight that underflows or comes near it -- logits
+      // more than 640 apart -- every slot takes the maximum of its own suffix: a weight of zero there would stand
+      // for a q that is not, and 0 / 0 would accept a token without target mass.)
       const double rest = sm.S_out / sm.S;
       double Zc = 1.0;
       double w[2], iq[2] = {0.0, 0.0};
@@ -1480,8 +1481,8 @@ __global__ __launch_bounds__(ACC_NT) void k_tree_accept(const T* __restrict__ lo
           iq[s] = 1.0 / v;
         }
       }
-      // the last child's is the smallest suffix
-      const bool safe = m > 0 && readlane_f64((m - 1) >> 6 ? iq[1] : iq[0], (m - 1) & 63) < 1e260;
+      const bool tiny = (lane < m && !(w[0] >= 1e-280)) || (lane + 64 < m && !(w[1] >= 1e-280));
+      const bool safe = __ballot(tiny) == 0;
       int acc = -1;
       for (int j = 0; j < m; ++j) {
         double q[2];                            // this lane's q_{u,j}

@@ -334,3 +334,64 @@ def test_nucleus_pattern_counts_edges(V, rows, top_p):
         x = np.where(rng.random(x.shape) < 0.02, x, -20.0)
     inp["target_logits"] = synth.f32_to_bf16_bits(x.astype(np.float32))
     _compare(inp, top_p=top_p)
+
+
+@pytest.mark.parametrize("top_p", [1.0, 0.9])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("logits", [(800.0, 0.0, 300.0), (0.0, -640.0, -300.0), (900.0, 0.0, 310.0, 305.0, 1.0)])
+def test_draft_logits_far_apart(logits, dtype, top_p):
+    """A child whose draft weight underflows beside the largest of all children, but not beside those still to try,
+    and whose token has no target mass: it is rejected, as r / q = 0 says."""
+    n = len(logits)
+    cfg = synth.scaled(synth.TINY_FP32, B=6, T=n + 1, depth=1, V=520, dtype=dtype, parents=(-1,) + (0,) * n)
+    inp = synth.accept_inputs(cfg, seed=n)
+    inp["child_logit"][:, 1:] = np.float32(logits)
+    inp["u_acc"][:, 1:] = np.float32(0.5)
+    inp["u_acc"][0, 2] = np.float32(1e-3)
+    x = synth.to_f64(inp["target_logits"], dtype)
+    for b in range(cfg.B):
+        x[b, 0, inp["tokens"][b, 2]] = -np.inf
+        if b % 2:                                # no mass on the later children either
+            x[b, 0, inp["tokens"][b, 3:]] = -np.inf
+    inp["target_logits"] = synth.as_dtype(x.astype(np.float32), dtype)
+    g, o = _compare(inp, top_p=top_p)
+    assert (o["acc_nodes"][:, 0] != 2).all()
+
+
+@pytest.mark.parametrize("what", ["nan", "inf", "none"])
+def test_nucleus_rows_that_the_counts_refuse(what):
+    """bf16 nucleus rows with a NaN, a +inf or no finite logit leave the pattern counts: their trajectories end with
+    tokens of the vocabulary, and the others of the batch, whose blocks share nothing with them, match the oracle."""
+    cfg = synth.scaled(synth.SHAPE_7B, B=8, T=12, depth=3, V=4104)
+    inp = synth.accept_inputs(cfg, seed=77)
+    bits = inp["target_logits"]
+    pat = dict(nan=0x7fc0, inf=0x7f80, none=0xff80)[what]
+    odd = (1, 4, 6)
+    for b in odd:
+        if what == "none":
+            bits[b] = pat
+        else:
+            bits[b, :, 5::700] = pat
+    g = _gpu_accept(inp, top_p=0.95)
+    for b in odd:
+        n = int(g["out_len"][b])
+        assert 1 <= n <= inp["max_depth"] + 1 and g["final_kind"][b] in (0, 1)
+        assert ((g["out_tokens"][b, :n] >= 0) & (g["out_tokens"][b, :n] < cfg.V)).all()
+    rows = [b for b in range(cfg.B) if b not in odd]
+    _compare(inp, rows=rows, top_p=0.95)
+
+
+@pytest.mark.parametrize("temperature", [1e-39, 1e-3, 1e3, 1e30])
+def test_nucleus_of_extreme_temperatures(temperature):
+    """1 / temperature that overflows (whose rows the pattern counts refuse), a nearly greedy one, and ones that make
+    the target uniform."""
+    cfg = synth.scaled(synth.SHAPE_7B, B=8, T=12, depth=3, V=4104)
+    inp = synth.accept_inputs(cfg, seed=78)
+    if temperature == 1e-39:
+        g = _gpu_accept(inp, temperature=temperature, top_p=0.95)
+        for b in range(cfg.B):
+            n = int(g["out_len"][b])
+            assert 1 <= n <= inp["max_depth"] + 1
+            assert ((g["out_tokens"][b, :n] >= 0) & (g["out_tokens"][b, :n] < cfg.V)).all()
+    else:
+        _compare(inp, temperature=temperature, top_p=0.95)
