@@ -163,6 +163,28 @@ template <int CTRL> __device__ __forceinline__ double dpp_f64(double v) {
   const int hi = __builtin_amdgcn_update_dpp((int)(u >> 32), (int)(u >> 32), CTRL, 0xf, 0xf, false);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
+// wave_sum_scatter of eight values with the sums in float64.
+__device__ __forceinline__ double wave_sum_scatter_f64(const float (&a)[8], int& j) {
+  const int lane = threadIdx.x & 63;
+  double b[4], c[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[k]), __float_as_uint(a[k + 4]), false, false);
+    b[k] = (double)__uint_as_float(r[0]) + (double)__uint_as_float(r[1]);
+  }
+  const bool hi16 = (lane & 16) != 0, hi8 = (lane & 8) != 0;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double keep = hi16 ? b[k + 2] : b[k], send = hi16 ? b[k] : b[k + 2];
+    c[k] = keep + __shfl_xor(send, 16, 64);
+  }
+  double v = (hi8 ? c[1] : c[0]) + __shfl_xor(hi8 ? c[0] : c[1], 8, 64);
+  v += dpp_f64<0xB1>(v);
+  v += dpp_f64<0x4E>(v);
+  v += dpp_f64<0x141>(v);
+  j = lane / 8;
+  return v;
+}
 __device__ __forceinline__ double readlane_f64(double v, int l) {
   const long long u = __double_as_longlong(v);
   const int lo = __builtin_amdgcn_readlane((int)u, l), hi = __builtin_amdgcn_readlane((int)(u >> 32), l);

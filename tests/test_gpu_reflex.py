@@ -295,3 +295,66 @@ def test_selection_edges(V, d, support):
     just more, supports of 1 and 64, and more than 4096 columns."""
     cfg = synth.scaled(synth.SHAPE_1P5B, B=3, H=2, V=V, d=d)
     _compare(synth.reflex_inputs(cfg, seed=V + support, support=support))
+
+
+def _cancelling_rows(e, group, rank, rng):
+    """Rows of powers of two with one non-zero column in each group of the first 4096 columns (so that every lane's
+    partial sum is exact in fp32) whose products with e cancel to 1e-8 of their size: each entry of the second half is
+    sized and signed to meet the running sum."""
+    P = np.zeros((rank, e.shape[0]), np.float32)
+    for j in range(rank):
+        cols = np.arange(0, min(e.shape[0], 4096), group)
+        cols = cols + rng.integers(0, group, cols.shape[0])
+        total = 0.0
+        for i, c in enumerate(cols):
+            if i > len(cols) // 2 and abs(total) < 1e-8 * len(cols):
+                break
+            want = total if i > len(cols) // 2 else rng.uniform(1.0, 2.0)
+            k = np.clip(np.round(np.log2(abs(want / float(e[c])))), -60, 60)
+            P[j, c] = np.float32((-np.sign(total * float(e[c])) or 1.0) * 2.0 ** k)
+            total += float(P[j, c]) * float(e[c])
+    return P
+
+
+@pytest.mark.parametrize("d", [1024, 4096, 8192])
+def test_sketch_of_cancelling_projections(d):
+    """The gated correction's sketch where the projections nearly cancel: the sums over a row are float64."""
+    cfg = synth.scaled(synth.TINY_FP32, B=2, H=2, d=d, V=512)
+    inp = synth.heads_inputs(cfg, seed=d)
+    gin = dict(synth.reflex_gate_inputs(cfg, seed=d))
+    m = np.random.default_rng(d).standard_normal(d).astype(np.float32)
+    gin["memory"] = np.broadcast_to(m, gin["memory"].shape).copy()
+    gin["P"] = _cancelling_rows(m, 4, 24, np.random.default_rng(d + 1))
+    prod = gin["P"].astype(np.float64) * m
+    assert 1e-10 < np.median(np.abs(prod.sum(1)) / np.abs(prod).sum(1)) < 1e-7
+    _, _, _, _, sk, _ = _gpu_heads_reflex(inp, gin)
+    want = oracle.sketch(m, gin["P"])
+    assert row_rel_err(sk.reshape(-1, 24), np.broadcast_to(want, (4, 24))).max() < 1e-6
+
+
+@pytest.mark.parametrize("d", [4096, 8192])
+def test_alignment_of_cancelling_projections(d):
+    """The delayed alignment of records whose feedback projections nearly cancel, against float64 sums of the stored
+    feedback vector."""
+    cfg = synth.scaled(synth.SHAPE_1P5B, B=1, H=1, V=4096, d=d)
+    inp = synth.reflex_inputs(cfg, seed=d, R=1)
+    _, gs, ge = _gpu(inp)
+    assert gs[0, 5] == 1
+    e = ge[0]
+    P = _cancelling_rows(e, 8, 12, np.random.default_rng(d))
+    prod = P.astype(np.float64) * e
+    x = prod.sum(1)
+    assert 1e-10 < np.median(np.abs(x) / np.abs(prod).sum(1)) < 1e-7
+    s_rec = np.random.default_rng(d + 1).standard_normal((1, 12)).astype(np.float32)
+    s_rec /= np.linalg.norm(s_rec)
+    al = torch.zeros((1, 1, 4), device="cuda")
+    mem = dev_tensor(inp["memory"])
+    _, e2 = sr.reflex_feedback(dev_tensor(inp["p_logits"]), dev_tensor(inp["p_row"]), dev_tensor(inp["q_logits"]),
+                               dev_tensor(inp["q_row"]), dev_tensor(inp["cand"]), dev_tensor(inp["y_star"]),
+                               dev_tensor(inp["traj"]), dev_tensor(inp["horizon"]), dev_tensor(inp["W"]), mem, rho=RHO,
+                               want_e=True, P=dev_tensor(P), rec_sketch=dev_tensor(s_rec), align=al, support=inp["support"])
+    assert np.array_equal(e2.cpu().numpy()[0], e)
+    want = float(s_rec[0].astype(np.float64) @ x / np.linalg.norm(x))
+    got = al.cpu().numpy()[0, 0]
+    assert got[0] == 1 and got[3] == 1
+    assert abs(got[1] - want) < 1e-6
