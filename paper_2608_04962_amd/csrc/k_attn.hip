@@ -1184,6 +1184,10 @@ __device__ __forceinline__ int attn_range_dma(unsigned char (&ring)[4][2 * DmaGe
     int l = 0;
     bool have = seg_begin(cs);
     bool ahead = false;                          // tile x + 2 was issued
+    // Nothing that the compiler tracks may be in flight here: it does not see the transfers, and would wait for such a
+    // load inside the loop, at every tile, with a vmcnt(0) that drains the tiles ahead (56 rows per KV head, 7B heads:
+    // 128 contexts of 1-8k keys 309 against 258 us, 256 lognormal contexts 406 against 333).
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0) alone, and known to the compiler
     if (np == 1) __builtin_amdgcn_s_setprio(3);   // the one DMA wave shares its SIMD with a compute wave
 #pragma unroll 1
     for (int x = -3; have; ++x) {
