@@ -73,11 +73,11 @@ def algorithmic(cfg, ctx_len, kernel):
 
 def attn_pieces(cfg, ctx_len):
     """Pieces of every (trajectory, KV head, row group) unit under the library's cut (sr_tree_verify_attn): row groups
-    of at most 224 query rows (bf16), all units' 64-key tiles (and 8 more for each unit) end to end over 256
-    ranges. Returns (pieces per unit, rows per KV head)."""
+    of at most 224 query rows (bf16), all units' 64-key tiles (and 6 more for each unit; 8 at D = 64) end to end over
+    256 ranges. Returns (pieces per unit, rows per KV head)."""
     R = cfg.T * (cfg.Hq // cfg.Hkv)
     ng = -(-R // 224) if (cfg.dtype == "bf16" and R > 224) else 1
-    cost = 8 if cfg.dtype == "bf16" else 1
+    cost = 1 if cfg.dtype != "bf16" else 8 if cfg.D == 64 else 6
     tiles = [-(-int(L) // 64) + -(-cfg.T // 64) for L in ctx_len for _ in range(cfg.Hkv * ng)]
     length = max(2, -(-(sum(tiles) + cost * len(tiles)) // 256))
     out, pos = [], 0

@@ -41,8 +41,7 @@ constexpr int ATT_ROWS = ATT_NW * ATT_RB * 32;  // query rows per block
 constexpr int ATT_BLOCKS = 256;        // ranges (blocks) of a call: one per CU
 constexpr int ATT_SEG_TILES = 1024;    // most tiles of a range: its page ids are held in LDS
 constexpr int ATT_TPP = ATT_KT / 16;   // pages per tile
-constexpr int ATT_WHOLE = 4;           // units of at most so many tiles are never cut
-constexpr int ATT_UNIT_COST = 8;       // what starting and writing a unit takes, in tiles (bf16)
+constexpr int ATT_WHOLE = 4;           // units of at most so many tiles are never cut (of more by attn_plan's rule)
 constexpr int ATT_MIN_TILES = 2;       // least tiles of a range (bf16)
 constexpr int ATT_BS = 16;             // tokens per page
 
@@ -1686,9 +1685,14 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   const long long units = (long long)d.B * d.Hkv * p.row_groups;
   const int most = (d.max_blocks * ATT_BS + ATT_KT - 1) / ATT_KT + (d.T + ATT_KT - 1) / ATT_KT;   // tiles of a unit
   p.whole = most <= ATT_WHOLE;
-  const long long tiles = units * (most + ATT_UNIT_COST);
   p.min_tiles = d.dtype == SR_BF16 ? ATT_MIN_TILES : 1;
-  p.unit_cost = d.dtype == SR_BF16 ? ATT_UNIT_COST : 1;
+  // What starting and writing a unit counts for, fitted on lognormal and uniform contexts with 1 to 7 waves of rows
+  // (1, 2, 3, 4, 6, 8, 12 tiles): 64 to 256 contexts of 56 to 112 rows, D = 128: 99, 180, 329 us with 6, 98, 181, 333
+  // with 8, 113, 190, 337 with 3; 224 rows 364 with 6, 366 with 8; D = 64, whose tiles are half the bytes: 128
+  // contexts of 32 rows 100 with 6, 101 with 8, 64 of 128 rows 62 with 6, 60 with 8. fp32 tiles are long: 8 contexts
+  // of 320 rows 237 with 1, 253 with 2.
+  p.unit_cost = d.dtype != SR_BF16 ? 1 : d.D == 64 ? 8 : 6;
+  const long long tiles = units * (most + p.unit_cost);
   const long long table = (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES;   // least ranges whose page ids fit the table
   const long long ranges = std::min(tiles, std::max<long long>(ATT_BLOCKS, table));
   p.n_ranges = ranges;
