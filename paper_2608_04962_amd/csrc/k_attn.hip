@@ -103,8 +103,8 @@ struct AttnGeom {
   static_assert(KVEC % NT == 0 && VITEMS % 64 == 0, "tile staging must split evenly over the block");
 };
 
-// Arguments of the attention kernels. A call's ranges have `len` tiles each (attn_plan_lds); with `whole` no unit
-// is cut and a range is the units that start in it.
+// Arguments of the attention kernels. A call's ranges have `len` tiles each (attn_len); with `whole` no unit is cut,
+// and a range is the units that start in it (1) or, where every unit has a block, one unit (2).
 template <typename T>
 struct AttnArgs {
   const T *q, *k_cache, *v_cache;
@@ -130,10 +130,11 @@ struct AttnPlanLds {
   int b;
 };
 
-// Length of all units together, in tiles; a unit counts as unit_cost tiles (what starting and writing it takes)
+// Length of all units together, in tiles (where every range is one unit: the ranges); a unit counts as unit_cost tiles (what starting and writing it takes)
 // more than it has, before its first (whole block; sums in float64 are exact here).
 template <typename T>
 __device__ __forceinline__ long long attn_total(AttnPlanLds& p, const AttnArgs<T>& a) {
+  if (a.whole == 2) return a.n_ranges;          // ranges of length 1
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double t = 0.0;
   for (int b = tid; b < a.B; b += ATT_NW * 64) t += (double)(unit_tiles(a.ctx_len[b], a.T_, a.max_blocks) + a.unit_cost);
@@ -186,6 +187,14 @@ template <typename T>
 __device__ __forceinline__ AttnStart attn_start(AttnPlanLds& p, const AttnArgs<T>& a, long long total, long long len, int r,
                                                 bool store) {
   AttnStart s = {0, 0, 1, 0, 0};
+  if (a.whole == 2) {                           // range r is unit r
+    const int units = a.Hkv * a.row_groups;
+    s.b = r / units;
+    s.j = r - s.b * units;
+    s.t = __builtin_amdgcn_readfirstlane(unit_tiles(a.ctx_len[s.b], a.T_, a.max_blocks));
+    s.left = 1;
+    return s;
+  }
   const long long start = (long long)r * len, end = min(total, start + len);
   if (start >= end) return s;
   attn_locate(p, a, start, store);
@@ -650,6 +659,7 @@ __device__ __forceinline__ int attn_range(int blk, int it, int grid, long long t
 // (265 for 256 trajectories of up to 16384 keys), nine blocks took two ranges: 0.59 ms where 256 ranges take 0.40.
 template <typename T>
 __device__ __forceinline__ long long attn_len(const AttnArgs<T>& a, long long total) {
+  if (a.whole == 2) return 1;
   const long long grid = gridDim.x, one = max((long long)a.min_tiles, (total + grid - 1) / grid);
   return one <= ATT_SEG_TILES ? one : max((long long)a.min_tiles, (total + a.n_ranges - 1) / a.n_ranges);
 }
@@ -1680,11 +1690,18 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   }
   p.row_groups = (p.R + p.group_rows - 1) / p.group_rows;
   // Ranges: one per CU; more only so that a range's page ids fit its LDS table at the longest contexts the block
-  // table can hold. A unit of at most ATT_WHOLE tiles is not worth cutting (a piece costs about as much to start
-  // and merge as it saves): such calls keep units whole and need no partial results.
+  // table can hold. Short units are not worth cutting (a piece costs about as much to start and
+  // merge as it saves): such calls keep them whole and need no partial results. With a block for every unit that is
+  // so the longer the more blocks the units fill: bf16, 256 units of 224 rows, contexts of hi / 8 to hi keys: whole
+  // 30, 48, 60, 87 us against cut 46, 59, 68, 86 at hi = 300, 1000, 1500, 2500; 128 of 112 rows 21, 28, 33, 41
+  // against 29, 32, 34, 37 at 300, 700, 1000, 1500; 64 of 224 rows 25, 30, 35 against 31, 33, 33 at 300, 500, 700; 32 of
+  // 192 rows 23, 28 against 25, 27 at 300, 500. More units, ranges of whole ones: 1024 of 56 rows 65, 77 against 70, 78 at
+  // 300, 500; 320 of 112 rows 36, 46 against 38, 45 at 200, 500. fp32, whose tiles are long: 256 units of 56 rows 84, 147
+  // against 92, 128 at 300, 700; 128 of 40 rows, D = 64, 37 against 28 at 300.
   const long long units = (long long)d.B * d.Hkv * p.row_groups;
   const int most = (d.max_blocks * ATT_BS + ATT_KT - 1) / ATT_KT + (d.T + ATT_KT - 1) / ATT_KT;   // tiles of a unit
-  p.whole = most <= ATT_WHOLE;
+  const bool each = units <= ATT_BLOCKS;
+  p.whole = most <= ATT_WHOLE + (d.dtype == SR_BF16 ? (each ? units * 5 / 64 : 3) : (each ? units / 128 : 0));
   p.min_tiles = d.dtype == SR_BF16 ? ATT_MIN_TILES : 1;
   // What starting and writing a unit counts for, fitted on lognormal and uniform contexts with 1 to 7 waves of rows
   // (1, 2, 3, 4, 6, 8, 12 tiles): 64 to 256 contexts of 56 to 112 rows, D = 128: 99, 180, 329 us with 6, 98, 181, 333
@@ -1695,7 +1712,7 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   const long long tiles = units * (most + p.unit_cost);
   const long long table = (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES;   // least ranges whose page ids fit the table
   const long long ranges = std::min(tiles, std::max<long long>(ATT_BLOCKS, table));
-  p.n_ranges = ranges;
+  p.n_ranges = p.whole && each ? units : ranges;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t row_bytes = (size_t)p.group_rows * (d.D + 2) * sizeof(float);   // one partial result
   const size_t work_bytes = up((size_t)(1 + d.B) * sizeof(long long));
@@ -1725,7 +1742,7 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
     if (p.n_ranges < table || p.n_ranges < std::min<long long>(units, ATT_BLOCKS)) {
       if (most <= ATT_SEG_TILES) {
         p.whole = true;
-        p.n_ranges = ranges;
+        p.n_ranges = each ? units : ranges;
       } else if (p.n_ranges < table) {
         p.n_ranges = table;
         p.min_bytes = p.full_bytes;
@@ -1733,6 +1750,7 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
     }
     sizes();
   }
+  p.each = p.whole && each;
   return p;
 }
 
@@ -1744,7 +1762,7 @@ static sr_status launch_attn_t(const sr_attn_desc& d, const AttnPlan& p, const v
   if (p.n_ranges > INT32_MAX / 4) return SR_ERR_INVALID;
   const AttnArgs<T> a = {(const T*)q, (const T*)kc, (const T*)vc, bt, cl, (const T*)kt, (const T*)vt, par, out, lse, po, pml,
                          work, d.B, d.T, d.Hq, d.Hkv, d.max_blocks, d.num_blocks, d.scale * kLog2e, p.R, p.row_groups,
-                         p.group_rows, (int)p.n_ranges, p.min_tiles, p.unit_cost, p.whole ? 1 : 0, p.by_unit ? 1 : 0};
+                         p.group_rows, (int)p.n_ranges, p.min_tiles, p.unit_cost, p.whole ? (p.each ? 2 : 1) : 0, p.by_unit ? 1 : 0};
   const dim3 grid((unsigned)std::min<long long>(p.n_ranges, ATT_BLOCKS));
   if constexpr (sizeof(T) == 2) {
     SR_LAUNCH("sr_tree_attn", (k_tree_attn_dma<D>), grid, dim3(ATT_NW * 64), 0, s, a);

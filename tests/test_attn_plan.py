@@ -14,7 +14,8 @@ class Plan(C.Structure):
     _fields_ = [("R", C.c_int), ("Rpad", C.c_int), ("row_groups", C.c_int), ("group_rows", C.c_int),
                 ("whole", C.c_bool), ("min_tiles", C.c_int), ("unit_cost", C.c_int), ("n_ranges", C.c_longlong),
                 ("part_o_bytes", C.c_size_t), ("part_ml_bytes", C.c_size_t), ("work_bytes", C.c_size_t),
-                ("min_bytes", C.c_size_t), ("full_bytes", C.c_size_t), ("by_unit", C.c_bool)]
+                ("min_bytes", C.c_size_t), ("full_bytes", C.c_size_t), ("each", C.c_bool),
+                ("by_unit", C.c_bool)]
 
 
 def _plan(d, avail):
@@ -46,6 +47,10 @@ def _check(d, avail):
     length = max(p.min_tiles, -(-total // grid))
     if length > SEG_TILES:
         length = max(p.min_tiles, -(-total // p.n_ranges))
+    assert p.each == (p.whole and units <= BLOCKS)
+    if p.each:                                 # a range for each unit, of any length
+        assert p.n_ranges == units
+        length = 1
     assert length <= SEG_TILES
     assert (most if p.whole else min(most, length)) <= SEG_TILES, "a segment's page ids overrun the LDS table"
     used = p.part_o_bytes + p.part_ml_bytes + p.work_bytes
@@ -75,6 +80,18 @@ def test_plan_over_workspaces(dtype, D, T, G):
                     assert p.min_bytes == least, "a workspace that was enough is refused"
                     if nch > 3:                # a long prefix is still cut, or there are units for half the blocks
                         assert not p.whole or B * Hkv * p.row_groups >= BLOCKS // 2
+
+
+def test_units_left_whole():
+    """Short units are left whole, the longer the more blocks they fill, and need no partial results; a unit past the
+    line is cut."""
+    for dtype, B, Hkv, tiles in ((_lib.SR_BF16, 64, 4, 24), (_lib.SR_BF16, 32, 4, 14), (_lib.SR_BF16, 1, 1, 4),
+                                 (_lib.SR_BF16, 65, 4, 7), (_lib.SR_BF16, 512, 8, 7), (_lib.SR_F32, 64, 4, 6),
+                                 (_lib.SR_F32, 1, 4, 4), (_lib.SR_F32, 128, 4, 4)):
+        for more in (0, 1):
+            d = _lib.AttnDesc(B, 8, 7 * Hkv, Hkv, 128, 16, 4 * (tiles - 1 + more), 1 << 20, dtype, 0.1)
+            p = _check(d, C.c_size_t(-1).value)
+            assert p.whole == (more == 0) and (p.part_o_bytes == 0) == p.whole, (dtype, B, Hkv, tiles, more)
 
 
 def test_partial_results_follow_the_rows():

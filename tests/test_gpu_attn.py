@@ -401,3 +401,48 @@ def test_python_takes_the_least_workspace():
         if size:
             with pytest.raises(ValueError, match="workspace"):
                 call(size - 256)
+
+
+@pytest.mark.parametrize("dt,B,Hkv,G,T,D,pages", [
+    ("bf16", 64, 4, 7, 8, 128, 92), ("bf16", 64, 4, 7, 8, 128, 93),      # 256 units of 24 and 25 tiles
+    ("bf16", 32, 4, 2, 65, 64, 48), ("bf16", 257, 1, 4, 5, 128, 24),     # two tree tiles; one unit past the blocks
+    ("bf16", 1, 1, 3, 9, 128, 12), ("f32", 64, 4, 4, 9, 64, 20), ("f32", 64, 4, 8, 9, 128, 20), ("f32", 3, 2, 5, 7, 64, 12)])
+def test_units_left_whole(dt, B, Hkv, G, T, D, pages):
+    """Short units that are not cut, a block for each or ranges of them, at the rule's line and one past it: contexts of
+    no key, one and the table's width, and trajectories with bad lengths and pages."""
+    rng = np.random.default_rng(pages)
+    lens = [int(x) for x in rng.integers(0, pages * 16 + 1, size=B)]
+    lens[0] = pages * 16
+    if B > 4:
+        lens[1], lens[2], lens[B - 1] = 0, 1, pages * 16
+    inp = _pooled_inputs(dt, B, T, Hkv * G, Hkv, D, lens, pages, 50, seed=pages)
+    if B > 8:
+        inp["ctx_len"][4] = pages * 16 + 1
+        inp["ctx_len"][5] = -3
+        inp["ctx_len"][6] = max(17, int(inp["ctx_len"][6]))
+        inp["block_table"][6, 1] = 50
+    t = {k: dev_tensor(v) for k, v in inp.items() if isinstance(v, np.ndarray)}
+    out, lse = sr.tree_verify_attn(t["q"], t["k_cache"], t["v_cache"], t["block_table"], t["ctx_len"], t["k_tree"],
+                                   t["v_tree"], t["parents"])
+    out, lse = out.cpu().numpy(), lse.cpu().numpy()
+    bad = {4, 5, 6} if B > 8 else set()
+    good = [b for b in range(B) if b not in bad]
+    for b in bad:
+        assert np.isnan(out[b]).all() and np.isnan(lse[b]).all()
+    nodes = [(b, u) for b in good[:6] + good[-6:] for u in range(T)]
+    ro, rl = _oracle(inp, nodes)
+    sel = ~np.isnan(ro[..., 0])
+    assert np.isfinite(out[good]).all()
+    assert row_rel_err(out[sel], ro[sel]).max() <= tol_for(dt)
+    assert np.abs(lse[sel] - rl[sel]).max() <= tol_for(dt)
+
+
+def test_cut_of_lognormal_contexts():
+    """256 trajectories of lognormal contexts with few rows: many units cut by the ranges of the 256 blocks."""
+    rng = np.random.default_rng(47)
+    lens = [int(x) for x in np.clip(np.exp(np.log(1000) + rng.standard_normal(256)), 1, 8192)]
+    inp = _pooled_inputs("bf16", 256, 8, 14, 2, 128, lens, 512, 60, seed=47)
+    t = {k: dev_tensor(v) for k, v in inp.items() if isinstance(v, np.ndarray)}
+    out, lse = sr.tree_verify_attn(t["q"], t["k_cache"], t["v_cache"], t["block_table"], t["ctx_len"], t["k_tree"],
+                                   t["v_tree"], t["parents"])
+    _check_nodes(inp, out.cpu().numpy(), lse.cpu().numpy(), [(b, u) for b in range(0, 256, 5) for u in (0, 7)])
