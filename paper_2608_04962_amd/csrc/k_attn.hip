@@ -654,14 +654,16 @@ __device__ __forceinline__ int attn_range(int blk, int it, int grid, long long t
   return r < n_act ? (int)r : -1;
 }
 
-// Tiles per range: one range per block, as long as a range's page ids fit the LDS table. The plan's number of ranges
-// allows for contexts of the block table's width, which the call's contexts mostly stay far below; cut into that many
-// (265 for 256 trajectories of up to 16384 keys), nine blocks took two ranges: 0.59 ms where 256 ranges take 0.40.
+// Tiles per range: one range per block, as long as a range's page ids fit the LDS table; else as many for every
+// block, in rounds. The plan's number of ranges allows for contexts of the block table's width, which the call's
+// contexts mostly stay far below; cut into that many (265 for 256 trajectories of up to 16384 keys), nine blocks took
+// two ranges: 0.59 ms where 256 ranges take 0.40.
 template <typename T>
 __device__ __forceinline__ long long attn_len(const AttnArgs<T>& a, long long total) {
   if (a.whole == 2) return 1;
-  const long long grid = gridDim.x, one = max((long long)a.min_tiles, (total + grid - 1) / grid);
-  return one <= ATT_SEG_TILES ? one : max((long long)a.min_tiles, (total + a.n_ranges - 1) / a.n_ranges);
+  const long long grid = gridDim.x, one = (total + grid - 1) / grid;
+  const long long ranges = min((long long)a.n_ranges, grid * ((one + ATT_SEG_TILES - 1) / ATT_SEG_TILES));
+  return max((long long)a.min_tiles, (total + ranges - 1) / ranges);
 }
 
 // fp32 inputs.
@@ -1689,8 +1691,8 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
     p.group_rows = ((p.R + ng - 1) / ng + 31) / 32 * 32;
   }
   p.row_groups = (p.R + p.group_rows - 1) / p.group_rows;
-  // Ranges: one per CU; more only so that a range's page ids fit its LDS table at the longest contexts the block
-  // table can hold. Short units are not worth cutting (a piece costs about as much to start and
+  // Ranges: one per CU; more, in whole rounds, only so that a range's page ids fit its LDS table at the longest
+  // contexts the block table can hold. Short units are not worth cutting (a piece costs about as much to start and
   // merge as it saves): such calls keep them whole and need no partial results. With a block for every unit that is
   // so the longer the more blocks the units fill: bf16, 256 units of 224 rows, contexts of hi / 8 to hi keys: whole
   // 30, 48, 60, 87 us against cut 46, 59, 68, 86 at hi = 300, 1000, 1500, 2500; 128 of 112 rows 21, 28, 33, 41
@@ -1711,7 +1713,8 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   p.unit_cost = d.dtype != SR_BF16 ? 1 : d.D == 64 ? 8 : 6;
   const long long tiles = units * (most + p.unit_cost);
   const long long table = (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES;   // least ranges whose page ids fit the table
-  const long long ranges = std::min(tiles, std::max<long long>(ATT_BLOCKS, table));
+  const long long rounds = (table + ATT_BLOCKS - 1) / ATT_BLOCKS;
+  const long long ranges = std::min(tiles, std::max<long long>(1, rounds) * ATT_BLOCKS);
   p.n_ranges = p.whole && each ? units : ranges;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t row_bytes = (size_t)p.group_rows * (d.D + 2) * sizeof(float);   // one partial result

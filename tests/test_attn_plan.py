@@ -44,9 +44,8 @@ def _check(d, avail):
     total = units * (most + p.unit_cost)
     # tiles of a range, as the kernels cut the longest contexts that the table can hold
     grid = min(p.n_ranges, BLOCKS)
-    length = max(p.min_tiles, -(-total // grid))
-    if length > SEG_TILES:
-        length = max(p.min_tiles, -(-total // p.n_ranges))
+    ranges = min(p.n_ranges, grid * -(-total // grid // SEG_TILES) if total > grid * SEG_TILES else grid)
+    length = max(p.min_tiles, -(-total // ranges))
     assert p.each == (p.whole and units <= BLOCKS)
     if p.each:                                 # a range for each unit, of any length
         assert p.n_ranges == units
@@ -80,6 +79,15 @@ def test_plan_over_workspaces(dtype, D, T, G):
                     assert p.min_bytes == least, "a workspace that was enough is refused"
                     if nch > 3:                # a long prefix is still cut, or there are units for half the blocks
                         assert not p.whole or B * Hkv * p.row_groups >= BLOCKS // 2
+
+
+def test_ranges_past_the_table_come_in_whole_rounds():
+    """More tiles than 256 blocks' tables hold: every block gets the same number of ranges."""
+    for dtype in (_lib.SR_F32, _lib.SR_BF16):
+        for B, mb in ((64, 2048), (64, 2100), (67, 7680), (1024, 1024), (300, 4096)):
+            d = _lib.AttnDesc(B, 8, 8, 8, 64, 16, mb, 1 << 20, dtype, 0.1)
+            p = _check(d, C.c_size_t(-1).value)
+            assert p.n_ranges > BLOCKS and p.n_ranges % BLOCKS == 0, p.n_ranges
 
 
 def test_units_left_whole():

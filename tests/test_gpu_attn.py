@@ -437,6 +437,22 @@ def test_units_left_whole(dt, B, Hkv, G, T, D, pages):
     assert np.abs(lse[sel] - rl[sel]).max() <= tol_for(dt)
 
 
+@pytest.mark.parametrize("dt,wide", [("f32", False), ("bf16", False), ("bf16", True)])
+def test_rounds_of_ranges(dt, wide):
+    """More tiles than the blocks' page-id tables hold at once: every block takes two ranges, one after the other."""
+    B, T, Hkv, G, D, mb = 66, 8, 8, 2, 64, 2048
+    lens = [mb * 16 - 7 * b for b in range(B)]
+    lens[7] = 5                                  # and a short one among them
+    inp = _pooled_inputs(dt, B, T, Hkv * G, Hkv, D, lens, mb, 30, seed=46)
+    assert sum(-(-n // 64) + 1 for n in lens) * Hkv > 256 * 1024
+    if wide:
+        inp["v_tree"][5:9] = synth.as_dtype((synth.to_f64(inp["v_tree"][5:9], dt) * 1e6).astype(np.float32), dt)
+    t = {k: dev_tensor(v) for k, v in inp.items() if isinstance(v, np.ndarray)}
+    out, lse = sr.tree_verify_attn(t["q"], t["k_cache"], t["v_cache"], t["block_table"], t["ctx_len"], t["k_tree"],
+                                   t["v_tree"], t["parents"])
+    _check_nodes(inp, out.cpu().numpy(), lse.cpu().numpy(), [(b, u) for b in (0, 7, 8, 33, 64, 65) for u in (0, T - 1)])
+
+
 def test_cut_of_lognormal_contexts():
     """256 trajectories of lognormal contexts with few rows: many units cut by the ranges of the 256 blocks."""
     rng = np.random.default_rng(47)
