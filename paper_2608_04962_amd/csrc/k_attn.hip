@@ -124,6 +124,12 @@ __device__ __forceinline__ int unit_tiles(int Lraw, int T_, int max_blocks) {
   return (Lraw + ATT_KT - 1) / ATT_KT + (T_ + ATT_KT - 1) / ATT_KT;
 }
 
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ long long uniform64(long long v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (long long)(((unsigned long long)hi << 32) | lo);
+}
+
 struct AttnPlanLds {
   double wsum[ATT_NW];
   long long off;
@@ -145,7 +151,7 @@ __device__ __forceinline__ long long attn_total(AttnPlanLds& p, const AttnArgs<T
 #pragma unroll
   for (int w = 0; w < ATT_NW; ++w) s += p.wsum[w];
   __syncthreads();
-  return (long long)s * a.Hkv * a.row_groups;
+  return uniform64((long long)s * a.Hkv * a.row_groups);
 }
 
 // Trajectory that position pos lies in and the position inside it (p.b, p.off); with `store` also every
@@ -199,9 +205,8 @@ __device__ __forceinline__ AttnStart attn_start(AttnPlanLds& p, const AttnArgs<T
   if (start >= end) return s;
   attn_locate(p, a, start, store);
   s.b = __builtin_amdgcn_readfirstlane(p.b);
-  const long long off = p.off;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)off), hi = __builtin_amdgcn_readfirstlane((uint32_t)(off >> 32));
-  const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+  const unsigned long long o = (unsigned long long)uniform64(p.off);
+  const uint32_t lo = (uint32_t)o, hi = (uint32_t)(o >> 32);
   s.t = __builtin_amdgcn_readfirstlane(unit_tiles(a.ctx_len[s.b], a.T_, a.max_blocks));
   const unsigned vt = (unsigned)(s.t + a.unit_cost);
   s.j = hi ? (int)(o / vt) : (int)(lo / vt);
@@ -403,6 +408,13 @@ __device__ __forceinline__ void attn_seg_regs(AttnSmem<AT, D>& sm, AttnMeta& met
   // ---- tile schedule: the segment's prefix tiles, then its tree tiles
   const int n_tiles = bad ? 0 : n;
 
+  // The addresses inside a tile are formed again for every tile at D = 128: kept, they are registers that spill, and a
+  // reload waits for the tile in flight (256 units of 224 rows, contexts of 750 to 6000 keys: 1249 -> 1012 us; 64 of
+  // 320 rows, 250 to 2000: 242 -> 208). At D = 64 they fit (128 of 40 rows, 750 to 6000: 154 against 161).
+  auto fresh = [](int v) __attribute__((always_inline)) -> int {
+    if constexpr (D == 128) asm volatile("" : "+v"(v));
+    return v;
+  };
   // global -> registers for tile i. A key past the range is loaded from the range's last key instead
   // (so nothing past ctx_len is read and every staged value is finite); its score is masked to -inf,
   // so its K row never matters and its V row is multiplied by an exact zero.
@@ -415,6 +427,7 @@ __device__ __forceinline__ void attn_seg_regs(AttnSmem<AT, D>& sm, AttnMeta& met
   const int tree_rowb = Hkv * G::ROWB;                                  // bytes between tree nodes
   auto load_tile = [&](const unsigned char* kb, const unsigned char* vb, int t0, int lim, auto off_of,
                        TileRegs<AT, D>& r) {
+    const int tid = fresh(threadIdx.x);
 #pragma unroll
     for (int j = 0; j < G::KVPT; ++j) {
       const int vi = tid + j * NT;
@@ -453,6 +466,7 @@ __device__ __forceinline__ void attn_seg_regs(AttnSmem<AT, D>& sm, AttnMeta& met
   // registers -> LDS stage (K row-major with chunk swizzle, V transposed with group swizzle; bf16 V is
   // widened to the fp32 V^T element exactly)
   auto stash = [&](int st, const TileRegs<AT, D>& r) {
+    const int tid = fresh(threadIdx.x);
 #pragma unroll
     for (int j = 0; j < G::KVPT; ++j) {
       const int vi = tid + j * NT;
@@ -565,6 +579,7 @@ __device__ __forceinline__ void attn_seg_regs(AttnSmem<AT, D>& sm, AttnMeta& met
       }
     }
     // O^T += V^T P^T; each V fragment feeds every row block
+    const int lane = fresh(threadIdx.x & 63), half = lane >> 5;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -663,7 +678,7 @@ __device__ __forceinline__ long long attn_len(const AttnArgs<T>& a, long long to
   if (a.whole == 2) return 1;
   const long long grid = gridDim.x, one = (total + grid - 1) / grid;
   const long long ranges = min((long long)a.n_ranges, grid * ((one + ATT_SEG_TILES - 1) / ATT_SEG_TILES));
-  return max((long long)a.min_tiles, (total + ranges - 1) / ranges);
+  return uniform64(max((long long)a.min_tiles, (total + ranges - 1) / ranges));
 }
 
 // fp32 inputs.
