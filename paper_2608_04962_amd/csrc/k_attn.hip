@@ -44,6 +44,8 @@ constexpr int ATT_TPP = ATT_KT / 16;   // pages per tile
 constexpr int ATT_WHOLE = 4;           // units of at most so many tiles are never cut (of more by attn_plan's rule)
 constexpr int ATT_MIN_TILES = 2;       // least tiles of a range (bf16)
 constexpr int ATT_BS = 16;             // tokens per page
+constexpr int ATT_PAIRS = 2 * ATT_BLOCKS;   // most whole units that are dealt to the blocks by length
+constexpr int ATT_PAIR_TILES = 26;     // and their most tiles
 
 // Arithmetic of the register-staged kernel. QKPL / PKPL: elements a lane supplies per MFMA slot for the
 // scores and for the weighted V sum.
@@ -104,7 +106,8 @@ struct AttnGeom {
 };
 
 // Arguments of the attention kernels. A call's ranges have `len` tiles each (attn_len); with `whole` no unit is cut,
-// and a range is the units that start in it (1) or, where every unit has a block, one unit (2).
+// and a range is the units that start in it (1), one unit, where every unit has a block (2), or one or two of at most
+// ATT_PAIRS units, the longest with the shortest (3).
 template <typename T>
 struct AttnArgs {
   const T *q, *k_cache, *v_cache;
@@ -134,13 +137,41 @@ struct AttnPlanLds {
   double wsum[ATT_NW];
   long long off;
   int b;
+  int tiles[ATT_PAIRS];                // units dealt by length: each trajectory's tiles, and the trajectories
+  unsigned short order[ATT_PAIRS];     // from the longest to the shortest
 };
 
-// Length of all units together, in tiles (where every range is one unit: the ranges); a unit counts as unit_cost tiles (what starting and writing it takes)
-// more than it has, before its first (whole block; sums in float64 are exact here).
+// Orders the trajectories (at most ATT_PAIRS) by falling tiles, equal ones by index. Whole block.
+template <typename T>
+__device__ __forceinline__ void attn_sort(AttnPlanLds& p, const AttnArgs<T>& a) {
+  const int tid = threadIdx.x;
+  static_assert(ATT_PAIRS <= ATT_NW * 64, "one trajectory per thread");
+  if (tid < a.B) p.tiles[tid] = unit_tiles(a.ctx_len[tid], a.T_, a.max_blocks);
+  __syncthreads();
+  if (tid < a.B) {
+    const int t = p.tiles[tid];
+    int rank = 0;
+    for (int c = 0; c < a.B; ++c) rank += p.tiles[c] > t || (p.tiles[c] == t && c < tid) ? 1 : 0;
+    p.order[rank] = (unsigned short)tid;
+  }
+  __syncthreads();
+}
+
+// Unit at position pos of that order (uniform): trajectory, number in it and tiles.
+__device__ __forceinline__ void attn_dealt(const AttnPlanLds& p, int units, int pos, int& b, int& j, int& t) {
+  const int i = pos / units;
+  b = __builtin_amdgcn_readfirstlane(p.order[i]);
+  j = pos - i * units;
+  t = __builtin_amdgcn_readfirstlane(p.tiles[b]);
+}
+
+// Length of all units together, in tiles; a unit counts as unit_cost tiles (what starting and writing it takes)
+// more than it has, before its first (whole block; sums in float64 are exact here). Where a range is one or two given
+// units: the number of ranges.
 template <typename T>
 __device__ __forceinline__ long long attn_total(AttnPlanLds& p, const AttnArgs<T>& a) {
-  if (a.whole == 2) return a.n_ranges;          // ranges of length 1
+  if (a.whole == 3) attn_sort(p, a);
+  if (a.whole >= 2) return a.n_ranges;          // ranges of length 1
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double t = 0.0;
   for (int b = tid; b < a.B; b += ATT_NW * 64) t += (double)(unit_tiles(a.ctx_len[b], a.T_, a.max_blocks) + a.unit_cost);
@@ -201,6 +232,11 @@ __device__ __forceinline__ AttnStart attn_start(AttnPlanLds& p, const AttnArgs<T
     s.left = 1;
     return s;
   }
+  if (a.whole == 3) {                           // units r and ATT_PAIRS - 1 - r
+    attn_dealt(p, a.Hkv * a.row_groups, r, s.b, s.j, s.t);
+    s.left = 1 << 30;
+    return s;
+  }
   const long long start = (long long)r * len, end = min(total, start + len);
   if (start >= end) return s;
   attn_locate(p, a, start, store);
@@ -241,7 +277,10 @@ __device__ __forceinline__ void attn_walk(AttnPlanLds& p, const AttnArgs<T>& a, 
   const int units = a.Hkv * a.row_groups;
   int k = 0;
   while (s.left > 0) {
-    if (s.j == units) {
+    if (a.whole == 3 && k > 0) {
+      if (k > 1 || ATT_PAIRS - 1 - r >= a.B * units) break;
+      attn_dealt(p, units, ATT_PAIRS - 1 - r, s.b, s.j, s.t);
+    } else if (s.j == units) {
       s.j = 0;
       if (++s.b == a.B) break;
       s.t = __builtin_amdgcn_readfirstlane(unit_tiles(a.ctx_len[s.b], a.T_, a.max_blocks));
@@ -675,7 +714,7 @@ __device__ __forceinline__ int attn_range(int blk, int it, int grid, long long t
 // two ranges: 0.59 ms where 256 ranges take 0.40.
 template <typename T>
 __device__ __forceinline__ long long attn_len(const AttnArgs<T>& a, long long total) {
-  if (a.whole == 2) return 1;
+  if (a.whole >= 2) return 1;
   const long long grid = gridDim.x, one = (total + grid - 1) / grid;
   const long long ranges = min((long long)a.n_ranges, grid * ((one + ATT_SEG_TILES - 1) / ATT_SEG_TILES));
   return uniform64(max((long long)a.min_tiles, (total + ranges - 1) / ranges));
@@ -1023,7 +1062,11 @@ __device__ __forceinline__ int attn_range_dma(unsigned char (&ring)[4][2 * DmaGe
   auto seg_begin = [&](SegIter& i) __attribute__((always_inline)) -> bool {
     const auto* a = kargs(kp);
     if (i.left <= 0) return false;
-    if (i.j == a->Hkv * a->row_groups) {
+    if (a->whole == 3 && !i.head) {
+      const int units = a->Hkv * a->row_groups;
+      if (i.k > 1 || ATT_PAIRS - 1 - r >= a->B * units) return false;
+      attn_dealt(plan, units, ATT_PAIRS - 1 - r, i.b, i.j, i.t);
+    } else if (i.j == a->Hkv * a->row_groups) {
       i.j = 0;
       if (++i.b == a->B) return false;
       i.t = unit_tiles(uload(a->ctx_len, i.b), a->T_, a->max_blocks);
@@ -1712,13 +1755,17 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   // so the longer the more blocks the units fill: bf16, 256 units of 224 rows, contexts of hi / 8 to hi keys: whole
   // 30, 48, 60, 87 us against cut 46, 59, 68, 86 at hi = 300, 1000, 1500, 2500; 128 of 112 rows 21, 28, 33, 41
   // against 29, 32, 34, 37 at 300, 700, 1000, 1500; 64 of 224 rows 25, 30, 35 against 31, 33, 33 at 300, 500, 700; 32 of
-  // 192 rows 23, 28 against 25, 27 at 300, 500. More units, ranges of whole ones: 1024 of 56 rows 65, 77 against 70, 78 at
-  // 300, 500; 320 of 112 rows 36, 46 against 38, 45 at 200, 500. fp32, whose tiles are long: 256 units of 56 rows 84, 147
-  // against 92, 128 at 300, 700; 128 of 40 rows, D = 64, 37 against 28 at 300.
+  // 192 rows 23, 28 against 25, 27 at 300, 500. Up to two for a block, dealt by length (cutting them costs every block a
+  // third start, and the merge): 512 of 56 rows 36, 44, 54, 61, 91 against 41, 54, 64, 70, 99 at hi = 300, 700, 1200,
+  // 1500, 2400; 344 of 84 rows 39, 47, 63 against 45, 54, 71 at 600, 1200, 2400; lognormal contexts of median hi / 6, whose
+  // longest unit sets the time: 512 of 56 rows 50, 70 against 49, 59 at 1200, 2400. More units, ranges of whole ones: 1024
+  // of 56 rows 65, 77 against 70, 78 at 300, 500. fp32, whose tiles are long: 256 units of 56 rows 84, 147 against 92,
+  // 128 at 300, 700; 128 of 40 rows, D = 64, 37 against 28 at 300.
   const long long units = (long long)d.B * d.Hkv * p.row_groups;
   const int most = (d.max_blocks * ATT_BS + ATT_KT - 1) / ATT_KT + (d.T + ATT_KT - 1) / ATT_KT;   // tiles of a unit
   const bool each = units <= ATT_BLOCKS;
-  p.whole = most <= ATT_WHOLE + (d.dtype == SR_BF16 ? (each ? units * 5 / 64 : 3) : (each ? units / 128 : 0));
+  const bool pairs = d.dtype == SR_BF16 && !each && units <= ATT_PAIRS && most <= ATT_PAIR_TILES;
+  p.whole = pairs || most <= ATT_WHOLE + (d.dtype == SR_BF16 ? (each ? units * 5 / 64 : 3) : (each ? units / 128 : 0));
   p.min_tiles = d.dtype == SR_BF16 ? ATT_MIN_TILES : 1;
   // What starting and writing a unit counts for, fitted on lognormal and uniform contexts with 1 to 7 waves of rows
   // (1, 2, 3, 4, 6, 8, 12 tiles): 64 to 256 contexts of 56 to 112 rows, D = 128: 99, 180, 329 us with 6, 98, 181, 333
@@ -1730,7 +1777,7 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   const long long table = (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES;   // least ranges whose page ids fit the table
   const long long rounds = (table + ATT_BLOCKS - 1) / ATT_BLOCKS;
   const long long ranges = std::min(tiles, std::max<long long>(1, rounds) * ATT_BLOCKS);
-  p.n_ranges = p.whole && each ? units : ranges;
+  p.n_ranges = p.whole && each ? units : pairs ? ATT_BLOCKS : ranges;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t row_bytes = (size_t)p.group_rows * (d.D + 2) * sizeof(float);   // one partial result
   const size_t work_bytes = up((size_t)(1 + d.B) * sizeof(long long));
@@ -1769,6 +1816,7 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
     sizes();
   }
   p.each = p.whole && each;
+  p.pairs = p.whole && pairs;
   return p;
 }
 
@@ -1780,7 +1828,7 @@ static sr_status launch_attn_t(const sr_attn_desc& d, const AttnPlan& p, const v
   if (p.n_ranges > INT32_MAX / 4) return SR_ERR_INVALID;
   const AttnArgs<T> a = {(const T*)q, (const T*)kc, (const T*)vc, bt, cl, (const T*)kt, (const T*)vt, par, out, lse, po, pml,
                          work, d.B, d.T, d.Hq, d.Hkv, d.max_blocks, d.num_blocks, d.scale * kLog2e, p.R, p.row_groups,
-                         p.group_rows, (int)p.n_ranges, p.min_tiles, p.unit_cost, p.whole ? (p.each ? 2 : 1) : 0, p.by_unit ? 1 : 0};
+                         p.group_rows, (int)p.n_ranges, p.min_tiles, p.unit_cost, p.whole ? (p.each ? 2 : p.pairs ? 3 : 1) : 0, p.by_unit ? 1 : 0};
   const dim3 grid((unsigned)std::min<long long>(p.n_ranges, ATT_BLOCKS));
   if constexpr (sizeof(T) == 2) {
     SR_LAUNCH("sr_tree_attn", (k_tree_attn_dma<D>), grid, dim3(ATT_NW * 64), 0, s, a);

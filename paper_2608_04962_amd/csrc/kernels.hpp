@@ -34,7 +34,7 @@ struct AttnPlan {
   long long n_ranges;   // ranges the call's tiles are cut into (at most)
   size_t part_o_bytes, part_ml_bytes, work_bytes;   // the scratch in use: partial results, the cut
   size_t min_bytes, full_bytes;   // least workspace a call takes; what the workspace query answers
-  bool each;        // whole units, and a range for each
+  bool each, pairs; // whole units, and a range for each, or for the longest with the shortest
   bool by_unit;     // partial results are numbered by range and unit (attn_slot), not two to a range
 };
 AttnPlan attn_plan(const sr_attn_desc& d, size_t avail);   // avail: bytes of workspace the call has

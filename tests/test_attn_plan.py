@@ -15,7 +15,7 @@ class Plan(C.Structure):
                 ("whole", C.c_bool), ("min_tiles", C.c_int), ("unit_cost", C.c_int), ("n_ranges", C.c_longlong),
                 ("part_o_bytes", C.c_size_t), ("part_ml_bytes", C.c_size_t), ("work_bytes", C.c_size_t),
                 ("min_bytes", C.c_size_t), ("full_bytes", C.c_size_t), ("each", C.c_bool),
-                ("by_unit", C.c_bool)]
+                ("pairs", C.c_bool), ("by_unit", C.c_bool)]
 
 
 def _plan(d, avail):
@@ -47,8 +47,8 @@ def _check(d, avail):
     ranges = min(p.n_ranges, grid * -(-total // grid // SEG_TILES) if total > grid * SEG_TILES else grid)
     length = max(p.min_tiles, -(-total // ranges))
     assert p.each == (p.whole and units <= BLOCKS)
-    if p.each:                                 # a range for each unit, of any length
-        assert p.n_ranges == units
+    if p.each or p.pairs:                      # a range for each unit, or for two, of any length
+        assert p.n_ranges == (units if p.each else BLOCKS) and (p.each or units <= 2 * BLOCKS and d.B <= 2 * BLOCKS)
         length = 1
     assert length <= SEG_TILES
     assert (most if p.whole else min(most, length)) <= SEG_TILES, "a segment's page ids overrun the LDS table"
@@ -94,7 +94,8 @@ def test_units_left_whole():
     """Short units are left whole, the longer the more blocks they fill, and need no partial results; a unit past the
     line is cut."""
     for dtype, B, Hkv, tiles in ((_lib.SR_BF16, 64, 4, 24), (_lib.SR_BF16, 32, 4, 14), (_lib.SR_BF16, 1, 1, 4),
-                                 (_lib.SR_BF16, 65, 4, 7), (_lib.SR_BF16, 512, 8, 7), (_lib.SR_F32, 64, 4, 6),
+                                 (_lib.SR_BF16, 65, 4, 26), (_lib.SR_BF16, 128, 4, 26), (_lib.SR_BF16, 129, 4, 7),
+                                 (_lib.SR_BF16, 512, 8, 7), (_lib.SR_F32, 64, 4, 6),
                                  (_lib.SR_F32, 1, 4, 4), (_lib.SR_F32, 128, 4, 4)):
         for more in (0, 1):
             d = _lib.AttnDesc(B, 8, 7 * Hkv, Hkv, 128, 16, 4 * (tiles - 1 + more), 1 << 20, dtype, 0.1)

@@ -406,6 +406,8 @@ def test_python_takes_the_least_workspace():
 @pytest.mark.parametrize("dt,B,Hkv,G,T,D,pages", [
     ("bf16", 64, 4, 7, 8, 128, 92), ("bf16", 64, 4, 7, 8, 128, 93),      # 256 units of 24 and 25 tiles
     ("bf16", 32, 4, 2, 65, 64, 48), ("bf16", 257, 1, 4, 5, 128, 24),     # two tree tiles; one unit past the blocks
+    ("bf16", 43, 8, 8, 25, 128, 100), ("bf16", 43, 8, 8, 25, 128, 101),  # 344 units of 26 and 27 tiles, dealt and cut
+    ("bf16", 512, 1, 3, 4, 64, 30), ("bf16", 11, 8, 5, 96, 128, 40),     # two for every block; three row groups each
     ("bf16", 1, 1, 3, 9, 128, 12), ("f32", 64, 4, 4, 9, 64, 20), ("f32", 64, 4, 8, 9, 128, 20), ("f32", 3, 2, 5, 7, 64, 12)])
 def test_units_left_whole(dt, B, Hkv, G, T, D, pages):
     """Short units that are not cut, a block for each or ranges of them, at the rule's line and one past it: contexts of
@@ -462,3 +464,20 @@ def test_cut_of_lognormal_contexts():
     out, lse = sr.tree_verify_attn(t["q"], t["k_cache"], t["v_cache"], t["block_table"], t["ctx_len"], t["k_tree"],
                                    t["v_tree"], t["parents"])
     _check_nodes(inp, out.cpu().numpy(), lse.cpu().numpy(), [(b, u) for b in range(0, 256, 5) for u in (0, 7)])
+
+
+def test_dealt_units_with_wide_values():
+    """Units dealt to the blocks by length, some with V outside fp16's range (recomputed in the block) and ties among
+    the lengths."""
+    lens = [int(x) for x in np.random.default_rng(48).choice([1, 64, 65, 500, 501, 900], size=100)]
+    inp = _pooled_inputs("bf16", 100, 6, 12, 3, 128, lens, 60, 64, seed=48)
+    vt = synth.to_f64(inp["v_tree"], "bf16")
+    vt[::7] *= 1e6
+    inp["v_tree"] = synth.as_dtype(vt.astype(np.float32), "bf16")
+    t = {k: dev_tensor(v) for k, v in inp.items() if isinstance(v, np.ndarray)}
+    call = lambda: sr.tree_verify_attn(t["q"], t["k_cache"], t["v_cache"], t["block_table"], t["ctx_len"], t["k_tree"],
+                                       t["v_tree"], t["parents"])
+    out, lse = call()
+    out2, lse2 = call()
+    assert torch.equal(out, out2) and torch.equal(lse, lse2)
+    _check_nodes(inp, out.cpu().numpy(), lse.cpu().numpy(), [(b, u) for b in range(100) for u in (0, 2, 5)])
