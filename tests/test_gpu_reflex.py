@@ -297,6 +297,30 @@ def test_selection_edges(V, d, support):
     _compare(synth.reflex_inputs(cfg, seed=V + support, support=support))
 
 
+@pytest.mark.parametrize("V,support", [(3072, 48), (3136, 48), (3456, 48), (3520, 48), (2048, 32), (2112, 33), (2432, 33),
+                                       (4672, 64), (4736, 64)])
+def test_selection_of_few_groups(V, support):
+    """Groups hardly more than the support, on both sides of the line to the full selection, with candidate counts
+    below and above what a wave's lanes hold."""
+    cfg = synth.scaled(synth.SHAPE_1P5B, B=8, H=2, V=V, d=64)
+    _compare(synth.reflex_inputs(cfg, seed=V + support, support=support))
+
+
+@pytest.mark.parametrize("V,d,support", [(16384, 72, 40)])
+def test_selection_of_many_equal(V, d, support):
+    """Hundreds of equal logits at the bound: more pairs than the lanes hold, ranked by id."""
+    cfg = synth.scaled(synth.SHAPE_1P5B, B=3, H=2, V=V, d=d)
+    inp = synth.reflex_inputs(cfg, seed=V + support, support=support)
+    rng = np.random.default_rng(5)
+    p = synth.to_f64(inp["p_logits"], "bf16")
+    for x in (p, inp["q_logits"]):
+        for r in range(inp["R"]):
+            x[r] = np.minimum(x[r], 40.0)
+            x[r, rng.choice(V, 600, replace=False)] = 40.0
+    inp["p_logits"] = synth.as_dtype(p.astype(np.float32), "bf16")
+    _compare(inp)
+
+
 def _cancelling_rows(e, group, rank, rng):
     """Rows of powers of two with one non-zero column in each group of the first 4096 columns (so that every lane's
     partial sum is exact in fp32) whose products with e cancel to 1e-8 of their size: each entry of the second half is
