@@ -239,6 +239,12 @@ def test_gated_correction_parity(name, over):
     assert 0 < opened < cfg.B * cfg.H
 
 
+@pytest.mark.parametrize("d", [64, 1024, 1088, 4096, 4160])
+def test_gated_correction_widths(d):
+    """Both sides of the widths at which the correction's block grows: four waves, sixteen, eight columns a thread."""
+    test_gated_correction_parity("1.5B-shape", dict(B=5, V=2048, d=d))
+
+
 def test_closed_gates_match_plain_proposal():
     cfg = synth.scaled(synth.SHAPE_1P5B, B=3, V=8000)
     inp = synth.heads_inputs(cfg, seed=8)
