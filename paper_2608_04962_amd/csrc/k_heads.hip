@@ -846,13 +846,17 @@ __global__ __launch_bounds__(256) void k_group_max(const float* __restrict__ log
   if (lane == 0) gmax[(size_t)row * ngroups + g] = v;
 }
 
-// Exact top-M of each row using its 64-column group maxima. With the groups dealt to the block's waves in turn, the
-// smallest over the waves of a wave's ceil(M / NW)-th largest group max, tau, has at least M group maxima at or
-// above it, so every top-M element is >= tau and lies in a group whose max is >= tau. Only those groups are read
+// Exact top-M of each row using its 64-column group maxima. Up to M = 32: with the groups dealt to the block's waves in
+// turn, the smallest over the waves of a wave's ceil(M / NW)-th largest group max, tau, has at least M group maxima at
+// or above it, so every top-M element is >= tau and lies in a group whose max is >= tau. Only those groups are read
 // (about three times M on N(0,1) rows) and their elements >= tau ranked. If more than TOPM_CAP elements qualify
 // (heavy ties), or a wave has fewer than ceil(M / NW) groups, the same block runs the full selection of the row.
 // Bound by latency: four barriers and two round trips to memory; a radix select of the M-th largest group max had
-// fifteen barriers (2374 groups a row: 16 rows, M = 32: 15.0 -> 10.8 us; 256 rows, M = 6: 10.9 -> 8.2 us).
+// fifteen barriers (2374 groups a row: 16 rows, M = 32: 15.0 -> 10.8 us; 256 rows, M = 6: 10.9 -> 8.2 us). Larger M
+// takes that radix select all the same, since the waves' bound leaves too much to rank (48 rows, M = 63: 96 groups 11 us
+// against 28, 2374 groups 13 against 16; M = 127: 192 groups 20 against 39, 2374 groups 18 against 36), and rows of
+// hardly more than M groups, whose bound is near the least group max whichever way, the full selection (M = 95, 96
+// groups: 27 against 101 us; M = 127, 128 groups: 35 against 138).
 constexpr int TOPM_MAXG = 4096;     // V <= 262144
 constexpr int TOPM_CAP = 2048;
 __global__ __launch_bounds__(TOPM_NT) void k_topm_grouped(const float* __restrict__ logits,
@@ -874,7 +878,9 @@ __global__ __launch_bounds__(TOPM_NT) void k_topm_grouped(const float* __restric
   const float* grow = gmax + (size_t)row * ngroups;
   if (tid == 0) { s_ng = 0; s_n = 0; }
   const int k = (M + NW - 1) / NW;
-  const bool few = k > ngroups / NW;            // uniform: some wave has fewer groups than that
+  // (uniform) some wave has fewer groups than that, or there are hardly more groups than M
+  const bool few = k > ngroups / NW || (M > 32 && 7 * ngroups < 8 * M);
+  const bool exact = !few && M > 32;
   // a thread's groups: consecutive threads on consecutive groups, or, with fewer groups than threads, dealt to the
   // waves in turn, so that every wave has its share of any row
   auto group_of = [&](int i) __attribute__((always_inline)) -> int {
@@ -888,19 +894,24 @@ __global__ __launch_bounds__(TOPM_NT) void k_topm_grouped(const float* __restric
     gk[i] = g < ngroups ? fkey(grow[g]) : 0u;
     top = max(top, gk[i]);
   }
-  // the k-th largest lane maximum of the wave (at most its k-th largest group max): k times the largest, each time
-  // taking one lane out
   uint32_t tau = 0;
-  for (int j = 0; j < k; ++j) {
-    const int m = wave_max_i32((int)(top ^ 0x80000000u));
-    tau = (uint32_t)m ^ 0x80000000u;
-    const unsigned long long at = __ballot(top == tau);
-    if (lane == __ffsll((long long)at) - 1) top = 0;
-  }
-  if (lane == 0) s_tau[wave] = tau;
-  __syncthreads();
+  if (exact) {
+    radix_kth([&](int i) { return fkey(grow[i]); }, ngroups, M, hist, scan, st);
+    tau = st.prefix;
+  } else {
+    // the k-th largest lane maximum of the wave (at most its k-th largest group max): k times the largest, each time
+    // taking one lane out
+    for (int j = 0; j < k; ++j) {
+      const int m = wave_max_i32((int)(top ^ 0x80000000u));
+      tau = (uint32_t)m ^ 0x80000000u;
+      const unsigned long long at = __ballot(top == tau);
+      if (lane == __ffsll((long long)at) - 1) top = 0;
+    }
+    if (lane == 0) s_tau[wave] = tau;
+    __syncthreads();
 #pragma unroll
-  for (int w = 0; w < NW; ++w) tau = min(tau, s_tau[w]);
+    for (int w = 0; w < NW; ++w) tau = min(tau, s_tau[w]);
+  }
   if (!few) {
 #pragma unroll
     for (int i = 0; i < GPL; ++i)

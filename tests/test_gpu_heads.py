@@ -244,3 +244,20 @@ def test_tree_build_selection_edges(V, T, depth, spread):
     assert ok.sum() >= 4
     np.testing.assert_array_equal(tok.cpu().numpy()[ok], ot[ok])
     np.testing.assert_array_equal(cl.cpu().numpy()[ok], ol[ok].astype(np.float32))
+
+
+@pytest.mark.parametrize("M,V", [(32, 2048), (33, 2112), (33, 2424), (33, 2440), (48, 3456), (48, 3528), (63, 4608), (63, 151936),
+                                 (95, 6080), (95, 12288), (127, 9280), (127, 9288), (127, 262144)])
+def test_top_m_lines(M, V):
+    """Both sides of the lines of the top-M selection: the waves' bound up to 32, a radix select of the group maxima
+    above, the full selection for hardly more groups than M."""
+    cfg = synth.scaled(synth.SHAPE_1P5B, B=4, T=M + 1, depth=1, V=V, H=1, dtype="f32")
+    inp = synth.head_logits_inputs(cfg, seed=M + V, std=1.5)
+    assert inp["max_children"] == M
+    tok, cl = sr.tree_build(dev_tensor(inp["logits"]), dev_tensor(inp["parents"]), dev_tensor(inp["root_token"]),
+                            dev_tensor(inp["u_tree"]), M)
+    ot, ol, margin = oracle.tree_build(inp["logits"], inp["parents"], inp["root_token"], inp["u_tree"])
+    ok = margin > 1e-9
+    assert ok.sum() >= 3
+    np.testing.assert_array_equal(tok.cpu().numpy()[ok], ot[ok])
+    np.testing.assert_array_equal(cl.cpu().numpy()[ok], ol[ok].astype(np.float32))
