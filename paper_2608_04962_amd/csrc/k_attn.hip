@@ -44,6 +44,7 @@ constexpr int ATT_TPP = ATT_KT / 16;   // pages per tile
 constexpr int ATT_WHOLE = 4;           // units of at most so many tiles are never cut (of more by attn_plan's rule)
 constexpr int ATT_MIN_TILES = 2;       // least tiles of a range (bf16)
 constexpr int ATT_BS = 16;             // tokens per page
+constexpr int ATT_PIECES = 64;         // pieces of a unit, where a few units share the blocks (more of long ones)
 constexpr int ATT_PAIRS = 2 * ATT_BLOCKS;   // most whole units that are dealt to the blocks by length
 constexpr int ATT_PAIR_TILES = 26;     // and their most tiles
 
@@ -1776,7 +1777,14 @@ AttnPlan attn_plan(const sr_attn_desc& d, size_t avail) {
   const long long tiles = units * (most + p.unit_cost);
   const long long table = (tiles + ATT_SEG_TILES - 1) / ATT_SEG_TILES;   // least ranges whose page ids fit the table
   const long long rounds = (table + ATT_BLOCKS - 1) / ATT_BLOCKS;
-  const long long ranges = std::min(tiles, std::max<long long>(1, rounds) * ATT_BLOCKS);
+  // One to three units are cut into fewer pieces than there are blocks, since the merge takes a unit's pieces one after
+  // the other (about a tenth of the time of a tile each): sqrt(8 tiles), at least ATT_PIECES (one unit of 64 rows,
+  // D = 64, of 8000, 16000, 30000 keys: 25, 25, 28 us with 64, 25, 32, 47 with 256; 448 rows, 120000 keys: 70 with 64, 65
+  // with 128 or 256).
+  long long pieces = ATT_PIECES;
+  while (pieces < ATT_BLOCKS && pieces * pieces < 8 * (long long)most) ++pieces;
+  const long long ranges = std::min(tiles, rounds > 1 ? rounds * ATT_BLOCKS
+                                                      : std::max(table, std::min<long long>(ATT_BLOCKS, pieces * units)));
   p.n_ranges = p.whole && each ? units : pairs ? ATT_BLOCKS : ranges;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t row_bytes = (size_t)p.group_rows * (d.D + 2) * sizeof(float);   // one partial result

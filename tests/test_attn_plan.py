@@ -90,6 +90,20 @@ def test_ranges_past_the_table_come_in_whole_rounds():
             assert p.n_ranges > BLOCKS and p.n_ranges % BLOCKS == 0, p.n_ranges
 
 
+def test_few_units_of_any_length():
+    """One to five units: 64 pieces each, more of long ones and where their page ids would not fit."""
+    for dtype in (_lib.SR_F32, _lib.SR_BF16):
+        for units in range(1, 6):
+            for mb in (200, 2000, 20000, 1 << 20, 1 << 22, 1 << 25):
+                d = _lib.AttnDesc(1, 8, 8 * units, units, 64, 16, mb, 1 << 20, dtype, 0.1)
+                p = _check(d, C.c_size_t(-1).value)
+                if mb <= 2000:
+                    assert p.n_ranges <= min(64 * units, BLOCKS)
+                assert p.n_ranges <= BLOCKS or p.n_ranges % BLOCKS == 0
+                least, _ = _least(d, p)
+                _check(d, least)
+
+
 def test_units_left_whole():
     """Short units are left whole, the longer the more blocks they fill, and need no partial results; a unit past the
     line is cut."""
