@@ -74,12 +74,22 @@ def algorithmic(cfg, ctx_len, kernel):
 def attn_pieces(cfg, ctx_len):
     """Pieces of every (trajectory, KV head, row group) unit under the library's cut (sr_tree_verify_attn): row groups
     of at most 224 query rows (bf16), all units' 64-key tiles (and 6 more for each unit; 8 at D = 64) end to end over
-    256 ranges. Returns (pieces per unit, rows per KV head)."""
+    256 ranges (fewer for one to three units); units short for their number are left whole. Returns (pieces per
+    unit, rows per KV head)."""
+    bf16 = cfg.dtype == "bf16"
     R = cfg.T * (cfg.Hq // cfg.Hkv)
-    ng = -(-R // 224) if (cfg.dtype == "bf16" and R > 224) else 1
-    cost = 1 if cfg.dtype != "bf16" else 8 if cfg.D == 64 else 6
+    ng = -(-R // 224) if (bf16 and R > 224) else 1
+    cost = 1 if not bf16 else 8 if cfg.D == 64 else 6
     tiles = [-(-int(L) // 64) + -(-cfg.T // 64) for L in ctx_len for _ in range(cfg.Hkv * ng)]
-    length = max(2, -(-(sum(tiles) + cost * len(tiles)) // 256))
+    units, most = len(tiles), -(-cfg.max_blocks * 16 // 64) + -(-cfg.T // 64)
+    each = units <= 256
+    whole = 4 + ((units * 5 // 64 if each else 3) if bf16 else (units // 128 if each else 0))
+    if bf16 and 256 < units <= 512:
+        whole = 26
+    if most <= whole:
+        return [1] * units, -(-R // ng)
+    per_unit = max(64, math.isqrt(8 * most - 1) + 1)
+    length = max(2 if bf16 else 1, -(-(sum(tiles) + cost * units) // min(256, per_unit * units)))
     out, pos = [], 0
     for t in tiles:
         out.append((pos + cost + t - 1) // length - (pos + cost) // length + 1)

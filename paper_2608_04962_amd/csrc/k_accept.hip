@@ -816,7 +816,7 @@ __device__ __attribute__((noinline)) void nuc_masked_sums(AccSmem& sm, const T* 
 // follow from counts times the patterns' weights, each weight evaluated once, in float64. Before, a row took a
 // max pass, a weight pass with 64-bit histogram atomics and a cut pass, with an exponential and a key for every
 // token of the last two. Bound by the LDS atomics (about 13 cycles per wave instruction:
-// 13 us of a row's 24 at V = 151936, was 75). Walk of 128 trajectories, 32 nodes, top_p 0.95: 0.276 -> 0.118 ms.
+// 13 us of a row's 24 at V = 151936, was 75). Walk of 128 trajectories, 32 nodes, top_p 0.95: 0.301 -> 0.129 ms.
 // A row is left to the radix path (row_stats_nuc, nucleus_bf16) when some count passes 65535 (the counts then
 // no longer add up to V), when it holds a NaN, +inf or no finite logit, and when the cut falls on -0.
 __device__ __forceinline__ uint32_t* nuc_pat() { return (uint32_t*)nuc_scratch<bf16_t>(); }

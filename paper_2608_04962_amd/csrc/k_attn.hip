@@ -9,8 +9,9 @@
 // sharing). A unit's keys are a row of 64-key tiles, the prefix's and then the tree's (under the ancestor
 // mask). All units' tiles, laid end to end, are cut into ranges of one length, one per block: every CU streams
 // the same number of tiles whatever the context lengths, and a unit is cut only where a range ends. The pieces
-// of a cut unit are partial results that k_attn_combine merges by log-sum-exp. Every block derives the cut from
-// ctx_len itself, so no kernel has to plan it first.
+// of a cut unit are partial results that k_attn_combine merges by log-sum-exp. Short units that fill the blocks are
+// left whole (attn_plan). Every block derives the cut, or its units, from ctx_len itself, so no kernel has to plan
+// it first.
 // Scores are computed transposed, S^T = K Q^T on 32x32 MFMA tiles: a lane then holds 16 keys of one query row, so
 // the row max needs one cross-half exchange; P stays in registers and feeds O^T = V^T P^T.
 //
@@ -300,13 +301,12 @@ __device__ __forceinline__ void attn_walk(AttnPlanLds& p, const AttnArgs<T>& a, 
 }
 
 // Per-block metadata of one segment: the validated id of every prefix page, the tree's parents and ancestor
-// masks (segments with tree tiles), an input-error flag and (DMA kernel) the largest V magnitude pattern.
+// masks (segments with tree tiles) and an input-error flag.
 struct AttnMeta {
   int pg[ATT_SEG_TILES * ATT_TPP];
   uint32_t anc[SR_MAX_TREE][SR_MAX_TREE / 32];
   int parent[SR_MAX_TREE];
   int bad;
-  int vwide;
 };
 
 // Fills AttnMeta for pages [page0, page1) of trajectory b and, with tree tiles, its tree; validates the block
@@ -314,7 +314,7 @@ struct AttnMeta {
 __device__ __forceinline__ bool attn_meta(AttnMeta& m, bool ctx_ok, bool tree, int page0, int page1, const int32_t* bt_b,
                                           const int32_t* par_b, int T_, int num_blocks) {
   const int tid = threadIdx.x, nt = blockDim.x;
-  if (tid == 0) { m.bad = ctx_ok ? 0 : 1; m.vwide = 0; }
+  if (tid == 0) m.bad = ctx_ok ? 0 : 1;
   __syncthreads();
   for (int p = page0 + tid; p < page1; p += nt) {
     int blk = bt_b[p];
@@ -1020,7 +1020,7 @@ __device__ __forceinline__ void attn_conv_share(int wave, int n_act, int np, int
 // own: the DMA waves are up to three tiles ahead of the others.
 struct SegIter {
   int b, j, t, ta, left, k;            // trajectory, unit, its tiles, first tile, virtual tiles left, ordinal
-  int n, slot, tree0, n_pre, key0, key1, L;
+  int n, slot, tree0, n_pre, key0, key1;
   bool ctx_ok, head;
 };
 
