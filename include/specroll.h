@@ -247,9 +247,11 @@ sr_status sr_tree_verify_attn_noalloc(const sr_attn_desc* desc,
  * its nucleus, as the paper's rollouts sample (App. C "Training protocol":
  * nucleus threshold 0.95): tokens ranked by (logit desc, id asc) stay while the
  * mass ranked before them is below top_p, and p is renormalised on them. Masses
- * of the cut are fp32 exponentials summed in 40-bit fixed point; the cut's
- * margin (distance of top_p to the cumulative mass around the last kept token)
- * enters min_margin.
+ * of the cut are float64 weights times token counts for bf16 rows, and fp32
+ * exponentials summed in 40-bit fixed point for fp32 rows and for bf16 rows with
+ * NaN, +inf or nothing finite, a value on more than 65535 tokens, or a cut at
+ * zero; the cut's margin (distance of top_p to the cumulative mass around the
+ * last kept token) enters min_margin.
  */
 typedef struct {
   int32_t B, T, V;       /* trajectories; tree nodes (1..SR_MAX_TREE); vocabulary */
